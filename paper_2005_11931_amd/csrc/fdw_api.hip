@@ -286,13 +286,38 @@ int choose_S(const fdw_ctx* c)
     return best;
 }
 
-__global__ void k_write_member(MemberDev* tab, int m, MemberDev val) { tab[m] = val; }
+// Members of a family are written to the device table in batches: the descriptions travel as the
+// kernel's arguments (16 of them, 3 KB).
+constexpr int kWriteBatch = 16;
+struct MemberBatch {
+    MemberDev v[kWriteBatch];
+};
+__global__ void k_write_members(MemberBatch b, MemberDev* tab, int words)
+{
+    const unsigned long long* src = (const unsigned long long*)b.v;
+    for (int k = threadIdx.x; k < words; k += blockDim.x) ((unsigned long long*)tab)[k] = src[k];
+}
 
+int write_members(fdw_ctx* c, int first, int n, hipStream_t s)
+{
+    static_assert(sizeof(MemberDev) % 8 == 0, "copied in 8-byte words");
+    for (int m = first; m < first + n; m += kWriteBatch) {
+        MemberBatch b;
+        const int k = std::min(kWriteBatch, first + n - m);
+        std::memcpy(b.v, &c->tab[m], sizeof(MemberDev) * (size_t)k);
+        hipLaunchKernelGGL(k_write_members, dim3(1), dim3(256), 0, s, b, c->tab_dev + m,
+                           k * (int)(sizeof(MemberDev) / 8));
+        HIPCHK(c, hipGetLastError());
+    }
+    return FDW_OK;
+}
+
+// Bring member m's description to the device table.  A context of one member needs no table (its
+// launches carry the description; the persistent launch writes it itself): small solves were bound
+// by these launches (64^2, 10 steps: 5 of 12).
 int push_member(fdw_ctx* c, int m, hipStream_t s = nullptr)
 {
-    hipLaunchKernelGGL(k_write_member, dim3(1), dim3(1), 0, s ? s : c->stream, c->tab_dev, m, c->tab[m]);
-    HIPCHK(c, hipGetLastError());
-    return FDW_OK;
+    return c->count == 1 ? FDW_OK : write_members(c, m, 1, s ? s : c->stream);
 }
 
 // Rebuild the launch decomposition for time block K (all members) and push the table.
@@ -308,11 +333,7 @@ int layout_for_K(fdw_ctx* c, int K, int S, hipStream_t st = nullptr)
         md.block_base = base;
         base += md.blocks;
     }
-    for (int i = 0; i < c->count; ++i) {
-        int rc = push_member(c, i, st);
-        if (rc) return rc;
-    }
-    return FDW_OK;
+    return c->count == 1 ? FDW_OK : write_members(c, 0, c->count, st ? st : c->stream);
 }
 
 // Non-temporal streaming pays off once a member's planes (state in and out, coefficients)
@@ -359,8 +380,7 @@ AdjLayout adj_layout(const fdw_ctx* c, const HostMember& hm, int ck)
     L.plane = align_up(plane_alloc(hm.ld, hm.ny, elem_size(c->dtype)), kAlign);
     L.plane64 = align_up((size_t)hm.ld * hm.ny * sizeof(double), kAlign);
     L.nck = (hm.N >= 1 && ck >= 1) ? (hm.N - 1) / ck : 0;  // checkpoints at ck, 2ck, ... < N
-    size_t b = align_up(sizeof(MemberDev), kAlign);
-    b += 8 * L.plane + 2 * L.plane64;
+    size_t b = 8 * L.plane + 2 * L.plane64;
     b += (size_t)(2 * L.nck) * L.plane;
     b += align_up(sizeof(int) * 2 * kMaxReceivers, kAlign);
     b += align_up(sizeof(int) * (size_t)(hm.ny + 1), kAlign);
@@ -371,11 +391,10 @@ AdjLayout adj_layout(const fdw_ctx* c, const HostMember& hm, int ck)
 }
 
 
-// Adjoint workspace: a MemberDev slot, the reverse state planes (u, du, lam, mu; two of each),
+// Adjoint workspace: the reverse state planes (u, du, lam, mu; two of each),
 // two FP64 gradient planes, the checkpoints (u, du) at steps ck, 2ck, ... < N, and the
 // receiver tables.
 struct AdjPlanes {
-    MemberDev* rep_dev = nullptr;
     void* planes_begin = nullptr;
     void* FU[2];
     void* FD[2];
@@ -402,7 +421,6 @@ AdjPlanes adj_carve(const fdw_ctx* c, const HostMember& hm, const AdjLayout& L, 
         return (void*)p;
     };
     const size_t es = elem_size(c->dtype);
-    P.rep_dev = (MemberDev*)take(sizeof(MemberDev));
     P.planes_begin = w + off;
     auto plane = [&]() { return plane_origin(take(L.plane), hm.ld, es); };
     for (int k = 0; k < 2; ++k) P.FU[k] = plane();
@@ -449,7 +467,7 @@ int record_hook(fdw_ctx* c, hipStream_t s)
     if (k >= L.nck) return FDW_OK;
     // slot addresses follow the workspace layout of the adjoint
     const size_t es = elem_size(c->dtype);
-    char* base = (char*)c->rec.ws + align_up(sizeof(MemberDev), kAlign) + 8 * L.plane + 2 * L.plane64;
+    char* base = (char*)c->rec.ws + 8 * L.plane + 2 * L.plane64;
     void* cu = plane_origin(base + (size_t)(2 * k) * L.plane, hm.ld, es);
     void* cd = plane_origin(base + (size_t)(2 * k + 1) * L.plane, hm.ld, es);
     return store_checkpoint(c, hm, cu, cd, hm.u[hm.cur], hm.d[hm.cur], s);
@@ -464,7 +482,7 @@ bool checkpoint_slot(fdw_ctx* c, const HostMember& hm, int64_t n, void** cu, voi
     const int64_t k = n / ck - 1;
     if (k >= L.nck) return false;
     const size_t es = elem_size(c->dtype);
-    char* base = (char*)c->rec.ws + align_up(sizeof(MemberDev), kAlign) + 8 * L.plane + 2 * L.plane64;
+    char* base = (char*)c->rec.ws + 8 * L.plane + 2 * L.plane64;
     *cu = plane_origin(base + (size_t)(2 * k) * L.plane, hm.ld, es);
     *cd = plane_origin(base + (size_t)(2 * k + 1) * L.plane, hm.ld, es);
     return true;
@@ -483,8 +501,7 @@ int do_start(fdw_ctx* c, int i, double* energy_out)
 {
     HostMember& hm = c->m[i];
     MemberDev& md = c->tab[i];
-    HIPCHK(c, launch_start<T>(&md, c->tab_dev + i, hm.u0, hm.u1, (T)hm.tau, energy_out != nullptr, 0, energy_out,
-                              c->red, c->stream));
+    HIPCHK(c, launch_start<T>(&md, hm.u0, hm.u1, (T)hm.tau, energy_out != nullptr, energy_out, c->red, c->stream));
     hm.n = 1;
     hm.cur = 0;
     if (hm.R > 0 && hm.traces && 1 < hm.N + 1)
@@ -503,6 +520,7 @@ int launch_block(fdw_ctx* c, int first, int nm, int K, bool energy, bool trace, 
     a.first = first;
     a.nmembers = nm;
     a.block_offset = c->tab[first].block_base;
+    a.one = c->tab[first];
     int total = 0;
     for (int i = first; i < first + nm; ++i) total += c->tab[i].blocks;
     a.total_blocks = total;
@@ -525,6 +543,7 @@ int launch_block(fdw_ctx* c, int first, int nm, int K, bool energy, bool trace, 
         for (int i = first; i < first + nm; ++i) {
             a.first = i;
             a.nmembers = 1;
+            a.one = c->tab[i];
             a.block_offset = c->tab[i].block_base;
             a.total_blocks = c->tab[i].blocks;
             HIPCHK(c, launch(a, c->m[i].face, a.total_blocks));
@@ -598,7 +617,7 @@ int run_blocks(fdw_ctx* c, int64_t steps, double* energy_dev, int64_t stride, in
         // and the last one).  It runs before the table is laid out for a new length: the sums
         // run over the waves of the decomposition that wrote the partials.
         if (energy_dev && gcount > 0 && (Kb != gK || gcount == gmax)) {
-            HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, 0, c->count, gK, energy_dev, stride, gstart,
+            HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, c->tab[0], 0, c->count, gK, energy_dev, stride, gstart,
                                                 health_word(c), s, 0, gcount));
             gcount = 0;
         }
@@ -641,7 +660,7 @@ int run_blocks(fdw_ctx* c, int64_t steps, double* energy_dev, int64_t stride, in
         k += Kb;
     }
     if (energy_dev && gcount > 0)
-        HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, 0, c->count, gK, energy_dev, stride, gstart, health_word(c), s,
+        HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, c->tab[0], 0, c->count, gK, energy_dev, stride, gstart, health_word(c), s,
                                             0, gcount));
     if (rm >= 0) {
         // the call's last launch wrote the ping-pong buffer: the table points at the member's own
@@ -676,6 +695,7 @@ int run_persistent(fdw_ctx* c, int64_t steps, double* energy_dev, int64_t stride
     for (const HostMember& hm : c->m)
         if (hm.face != face_mode) return fail(c, FDW_ENOTSUP, "persistent batch needs one coefficient layout");
     int rc = layout_for_K(c, K, c->S_eff, s);
+    if (rc == FDW_OK && c->count == 1) rc = write_members(c, 0, 1, s);  // this launch reads the table
     if (rc) return rc;
     const int64_t phases = steps / K;
     const int64_t tail = steps - phases * K;
@@ -690,6 +710,7 @@ int run_persistent(fdw_ctx* c, int64_t steps, double* energy_dev, int64_t stride
         StepArgs a;
         a.eslot = 0;
         a.table = c->tab_dev;
+        a.one = c->tab[0];
         a.first = 0;
         a.nmembers = c->count;
         a.block_offset = 0;
@@ -708,7 +729,7 @@ int run_persistent(fdw_ctx* c, int64_t steps, double* energy_dev, int64_t stride
         x.err = sync_err_word(c);
         HIPCHK(c, launch_step_persistent<T>(a, K, c->C, face_mode, ph, grid, c->barrier, x, s));
         if (energy_dev)
-            HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, 0, c->count, K, energy_dev, stride, k + (int64_t)(ph - 1) * K,
+            HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, c->tab[0], 0, c->count, K, energy_dev, stride, k + (int64_t)(ph - 1) * K,
                                                 health_word(c), s, (ph - 1) & 1));
         c->ctx_step += (int64_t)ph * K;
         c->launches += ph;
@@ -800,7 +821,7 @@ int step_n_impl(fdw_ctx* c, int64_t n, double* energy_dev)
                     rc = launch_block<T>(c, i, 1, 1, e != nullptr, any_trace(c), c->stream);
                     if (rc) return rc;
                     if (e)
-                        HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, i, 1, 1, energy_dev, n, 0, health_word(c),
+                        HIPCHK(c, launch_energy_finalize<T>(c->tab_dev, c->tab[i], i, 1, 1, energy_dev, n, 0, health_word(c),
                                                             c->stream));
                     // this member alone advanced: its parity and offset move relative to the context
                     hm.n += 1;
@@ -1187,7 +1208,9 @@ int fdw_step_n(fdw_ctx* c, int64_t n, double* energy_dev)
     const bool check = energy_dev && c->check_energy && n > 0;
     // both words (failure detection, barrier timeout) start at zero; a test can mark the
     // barrier word as if the persistent launch had timed out (no kernel waits on it)
-    HIPCHK(c, launch_fill_bytes(health_word(c), 2 * sizeof(int), c->stream));
+    // (cleared only in calls that may read them back)
+    if (energy_dev || c->batch_mode == 1 || c->test_flag_barrier)
+        HIPCHK(c, launch_fill_bytes(health_word(c), 2 * sizeof(int), c->stream));
     if (c->test_flag_barrier) HIPCHK(c, launch_set_int(sync_err_word(c), 1, c->stream));
     c->used_persistent = false;
     const int rc = (c->dtype == FDW_F32) ? step_n_impl<float>(c, n, energy_dev) : step_n_impl<double>(c, n, energy_dev);
@@ -1612,7 +1635,6 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
     int* rcol = P.rcol;
     int* rid = P.rid;
     int* status = P.status;
-    MemberDev* rep_dev = P.rep_dev;
     hipStream_t s = c->stream;
     const int64_t N = hm.N;
     // The forward run of this member stored every checkpoint into this workspace and stopped
@@ -1653,10 +1675,10 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
         rep.cur0 = 0;
         rep.n_offset = 0;
         rep.block_base = 0;
-        HIPCHK(c, launch_start<T>(&rep, rep_dev, hm.u0, hm.u1, (T)hm.tau, 0, 0, nullptr, c->red, s));
+        HIPCHK(c, launch_start<T>(&rep, hm.u0, hm.u1, (T)hm.tau, 0, nullptr, c->red, s));
         int64_t n = 1;
         const int Kf = choose_K(c);
-        int pushedK = -1;
+        int laidK = -1;
         auto store_ckpt = [&](int64_t step) -> int {
             const int64_t k = step / ck - 1;
             return store_checkpoint(c, hm, CU[k], CD[k], FU[cur], FD[cur], s);
@@ -1668,15 +1690,14 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
         while (n < N) {
             const int64_t next = std::min<int64_t>(N, (n / ck + 1) * ck);
             const int Kb = (int)std::min<int64_t>(Kf, next - n);
-            if (Kb != pushedK) {
+            if (Kb != laidK) {
                 decompose(c, hm, rep, c->S_eff, Kb);
-                hipLaunchKernelGGL(k_write_member, dim3(1), dim3(1), 0, s, rep_dev, 0, rep);
-                HIPCHK(c, hipGetLastError());
-                pushedK = Kb;
+                laidK = Kb;
             }
             StepArgs a;
             a.eslot = 0;
-            a.table = rep_dev;
+            a.table = nullptr;
+            a.one = rep;
             a.first = 0;
             a.nmembers = 1;
             a.block_offset = 0;

@@ -59,9 +59,11 @@ struct MemberDev {
                             // with non-temporal accesses (0: keep them cacheable)
 };
 
-// Per-launch arguments of the streaming stencil.
+// Per-launch arguments of the streaming stencil.  A launch over a single member carries that
+// member's description itself (`one`): its kernels read it with their arguments instead of following
+// the table pointer, and the table need not be written before the launch.
 struct StepArgs {
-    const MemberDev* table;
+    const MemberDev* table;  // launches over several members
     int nmembers;      // members covered by this launch (table[first .. first+nmembers-1])
     int first;
     int block_offset;  // added to blockIdx.x before the member lookup
@@ -73,6 +75,7 @@ struct StepArgs {
     int stream_nt;     // 1: non-temporal loads of the state rows (float; see MemberDev for the stores)
     int reverse;       // 1: walk the launch's blocks in reverse order (alternating item order)
     int eslot;         // energy-partial slot the launch writes (time block within a finalisation group)
+    MemberDev one;     // the member, when nmembers == 1 (the persistent launch reads the table)
 };
 
 // Extra arguments of the persistent launch: where its energies go (as for
@@ -102,7 +105,8 @@ template <typename T>
 // first energy of the call (energy_base[row * energy_stride], row = MemberDev::energy_row)
 // slot: the partial slot holding the first time block; nslots time blocks of `levels` steps
 // each, in slots slot .. slot + nslots - 1, their energies at energy_offset + j * levels + t
-hipError_t launch_energy_finalize(const MemberDev* table, int first, int nmembers, int levels, double* energy_base,
+// one: the member's description when nmembers == 1 (table is not read then)
+hipError_t launch_energy_finalize(const MemberDev* table, const MemberDev& one, int first, int nmembers, int levels, double* energy_base,
                                   int64_t energy_stride, int64_t energy_offset, int* health, hipStream_t s,
                                   int slot = 0, int nslots = 1);
 
@@ -110,8 +114,8 @@ template <typename T>
 hipError_t launch_prepare_coeff(const MemberDev* m_host, const void* h1, const void* h2, int face, double* red,
                                 hipStream_t s);
 template <typename T>
-hipError_t launch_start(const MemberDev* m_host, const MemberDev* m_dev, const void* u0, const void* u1, T tau,
-                        int want_energy, int want_trace, double* energy_out, double* red, hipStream_t s);
+hipError_t launch_start(const MemberDev* m_host, const void* u0, const void* u1, T tau, int want_energy,
+                        double* energy_out, double* red, hipStream_t s);
 template <typename T>
 hipError_t launch_state_energy(const MemberDev* m_host, int cur, double* red, double* out, hipStream_t s);
 template <typename T>

@@ -119,14 +119,15 @@ __device__ double level_partial_sum(const MemberDev& M, int slot, int t, double*
     return r;
 }
 
-__global__ __launch_bounds__(256) void k_energy_finalize(const MemberDev* table, int first, double* energy_base,
-                                                         int64_t energy_stride, int64_t energy_offset, int* health,
-                                                         int slot)
+// (`one` is the first argument: member_at finds it at offset 0)
+__global__ __launch_bounds__(256) void k_energy_finalize(MemberDev one, const MemberDev* table, int first,
+                                                         double* energy_base, int64_t energy_stride,
+                                                         int64_t energy_offset, int* health, int slot)
 {
     const int t = blockIdx.x;
     const int m = first + blockIdx.y;
     const int j = blockIdx.z;  // time block within the group
-    const MemberDev& M = table[m];
+    const MemberDev M = member_copy(member_at(table, m, gridDim.y == 1, 0));
     __shared__ double red[256];
     const double E = level_partial_sum(M, slot + j, t, red) * M.escale;
     const int64_t off = energy_offset + (int64_t)j * gridDim.x + t;
@@ -147,18 +148,18 @@ __global__ __launch_bounds__(256) void k_energy_finalize(const MemberDev* table,
 }
 
 template <typename T>
-hipError_t launch_energy_finalize(const MemberDev* table, int first, int nmembers, int levels, double* energy_base,
-                                  int64_t energy_stride, int64_t energy_offset, int* health, hipStream_t s, int slot,
-                                  int nslots)
+hipError_t launch_energy_finalize(const MemberDev* table, const MemberDev& one, int first, int nmembers, int levels,
+                                  double* energy_base, int64_t energy_stride, int64_t energy_offset, int* health,
+                                  hipStream_t s, int slot, int nslots)
 {
-    hipLaunchKernelGGL(k_energy_finalize, dim3(levels, nmembers, nslots), dim3(256), 0, s, table, first, energy_base,
+    hipLaunchKernelGGL(k_energy_finalize, dim3(levels, nmembers, nslots), dim3(256), 0, s, one, table, first, energy_base,
                        energy_stride, energy_offset, health, slot);
     return hipGetLastError();
 }
-template hipError_t launch_energy_finalize<float>(const MemberDev*, int, int, int, double*, int64_t, int64_t, int*,
-                                                  hipStream_t, int, int);
-template hipError_t launch_energy_finalize<double>(const MemberDev*, int, int, int, double*, int64_t, int64_t, int*,
-                                                   hipStream_t, int, int);
+template hipError_t launch_energy_finalize<float>(const MemberDev*, const MemberDev&, int, int, int, double*, int64_t,
+                                                  int64_t, int*, hipStream_t, int, int);
+template hipError_t launch_energy_finalize<double>(const MemberDev*, const MemberDev&, int, int, int, double*, int64_t,
+                                                   int64_t, int*, hipStream_t, int, int);
 
 // ------------------------------------------------------------------------------------------
 // Block reduction helpers (fixed order) for the generic two-stage reductions.
@@ -371,8 +372,8 @@ __global__ __launch_bounds__(256) void k_start(MemberDev M, const T* __restrict_
 }
 
 template <typename T>
-hipError_t launch_start(const MemberDev* m, const MemberDev* m_dev, const void* u0, const void* u1, T tau,
-                        int want_energy, int want_trace, double* energy_out, double* red, hipStream_t s)
+hipError_t launch_start(const MemberDev* m, const void* u0, const void* u1, T tau, int want_energy,
+                        double* energy_out, double* red, hipStream_t s)
 {
     const int64_t total = (int64_t)m->ld * m->ny;
     int blocks = (int)((total + 255) / 256);
@@ -386,14 +387,12 @@ hipError_t launch_start(const MemberDev* m, const MemberDev* m_dev, const void* 
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    (void)m_dev;
-    (void)want_trace;
     return hipSuccess;
 }
-template hipError_t launch_start<float>(const MemberDev*, const MemberDev*, const void*, const void*, float, int, int,
-                                        double*, double*, hipStream_t);
-template hipError_t launch_start<double>(const MemberDev*, const MemberDev*, const void*, const void*, double, int,
-                                         int, double*, double*, hipStream_t);
+template hipError_t launch_start<float>(const MemberDev*, const void*, const void*, float, int, double*, double*,
+                                        hipStream_t);
+template hipError_t launch_start<double>(const MemberDev*, const void*, const void*, double, int, double*, double*,
+                                         hipStream_t);
 
 // ------------------------------------------------------------------------------------------
 // E^{n-1/2} of a stored state (u^n, du^n): escale * sum du^2 - (u - du) L(u).

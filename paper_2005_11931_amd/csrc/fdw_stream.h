@@ -7,6 +7,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+
 namespace fdw {
 
 // ------------------------------------------------------------------------------------------
@@ -291,11 +293,11 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
 
     const int r0 = seg * M.seg_rows;
     const int r1 = min(r0 + M.seg_rows, ny);
-    const int cur = M.cur0 ^ parity;
-    const T* __restrict__ uin = (const T*)M.u[cur];
-    const T* __restrict__ din = (const T*)M.d[cur];
-    T* __restrict__ uout = (T*)M.u[cur ^ 1];
-    T* __restrict__ dout = (T*)M.d[cur ^ 1];
+    const bool cur = ((M.cur0 ^ parity) & 1) != 0;
+    const T* __restrict__ uin = (const T*)(cur ? M.u[1] : M.u[0]);
+    const T* __restrict__ din = (const T*)(cur ? M.d[1] : M.d[0]);
+    T* __restrict__ uout = (T*)(cur ? M.u[0] : M.u[1]);
+    T* __restrict__ dout = (T*)(cur ? M.d[0] : M.d[1]);
     const T* __restrict__ hp = (const T*)M.h;
     const T* __restrict__ hyp = (const T*)M.hy;
     const T ax = (T)M.ax, ay = (T)M.ay;
@@ -645,6 +647,32 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
     }
 }
 
+// A member's description as read-only (constant) memory, so that its fields are scalar loads: from
+// the kernel's own arguments (`offset` bytes into them) for a launch over one member - one memory
+// round trip less at the head of every launch - else from the table.
+__device__ __forceinline__ ConstPtr<MemberDev> member_at(const MemberDev* table, int m, bool by_value, int offset)
+{
+    typedef const __attribute__((address_space(4))) char* Bytes;
+    return by_value ? (ConstPtr<MemberDev>)((Bytes)__builtin_amdgcn_kernarg_segment_ptr() + offset)
+                    : (ConstPtr<MemberDev>)(table + m);
+}
+
+// Field by field copy out of constant memory (the fields a kernel does not use are never loaded)
+__device__ __forceinline__ MemberDev member_copy(ConstPtr<MemberDev> p)
+{
+    MemberDev m;
+    m.nx = p->nx, m.ny = p->ny, m.ld = p->ld, m.face = p->face;
+    m.strips = p->strips, m.segs = p->segs, m.seg_rows = p->seg_rows, m.waves = p->waves, m.blocks = p->blocks;
+    m.block_base = p->block_base, m.cur0 = p->cur0, m.energy_row = p->energy_row, m.R = p->R;
+    m.n_offset = p->n_offset, m.trace_rows = p->trace_rows;
+    m.ax = p->ax, m.ay = p->ay, m.escale = p->escale;
+    m.u[0] = p->u[0], m.u[1] = p->u[1], m.d[0] = p->d[0], m.d[1] = p->d[1];
+    m.h = p->h, m.hy = p->hy;
+    m.rec_rowptr = p->rec_rowptr, m.rec_col = p->rec_col, m.rec_id = p->rec_id;
+    m.traces = p->traces, m.epart = p->epart, m.epart_stride = p->epart_stride, m.stream_nt = p->stream_nt;
+    return m;
+}
+
 __device__ __forceinline__ int find_member(const MemberDev* table, int first, int nmembers, int gb)
 {
     int m = first;
@@ -662,8 +690,9 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock, (sizeof(T) == 8 && C ==
     int lb = xcd_remap(blockIdx.x, a.total_blocks);
     if (a.reverse) lb = a.total_blocks - 1 - lb;
     const int gb = lb + a.block_offset;
-    const int m = find_member(a.table, a.first, a.nmembers, gb);
-    const MemberDev& M = a.table[m];
+    const bool one = a.nmembers == 1;
+    const int m = one ? a.first : find_member(a.table, a.first, a.nmembers, gb);
+    const MemberDev M = member_copy(member_at(a.table, m, one, offsetof(StepArgs, one)));
     const int wave = (gb - M.block_base) * kWavesPerBlock + wave_in_block();
     if (wave >= M.waves) return;
     sweep_item<T, K, C, FACE, MODE>(M, wave, a.parity, a.ctx_step, a.eslot);

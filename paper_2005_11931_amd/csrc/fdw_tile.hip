@@ -48,8 +48,9 @@ __global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArg
     const int w = wave_in_block();
     const int lane = threadIdx.x & 63;
     const int gb = (int)blockIdx.x + a.block_offset;
-    const int m = (a.nmembers == 1) ? a.first : find_member(a.table, a.first, a.nmembers, gb);
-    const MemberDev& M = a.table[m];
+    const bool one = a.nmembers == 1;
+    const int m = one ? a.first : find_member(a.table, a.first, a.nmembers, gb);
+    const MemberDev M = member_copy(member_at(a.table, m, one, offsetof(StepArgs, one)));
     // Every field of the member the prologue needs is read here, before any of them is used, so
     // that all table reads are one round of scalar loads ahead of the plane loads (left to the
     // scheduler they were split into several dependent rounds around the index arithmetic).
