@@ -57,8 +57,10 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     const int strip = wave % a.strips;
     const int seg = wave / a.strips;
     const int cb = strip * Wv - Hx + lane * C;
-    const bool lane_live = (cb >= 0) && (cb < ld);
-    const bool lane_owned = lane_live && (lane * C >= Hx) && (lane * C < Hx + Wv);
+    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
+    // up to three that share a wider lane vector with the last column are written (as 0).
+    const bool lane_live = (cb >= 0) && (cb < nx);
+    const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane * C >= Hx) && (lane * C < Hx + Wv);
     T colm[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) colm[c] = ((cb + c >= 1) && (cb + c <= nx - 2)) ? T(1) : T(0);

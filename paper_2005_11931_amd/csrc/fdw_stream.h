@@ -285,8 +285,10 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
     const int strip = wave % M.strips;
     const int seg = wave / M.strips;
     const int cb = strip * Wv - Hx + lane * C;
-    const bool lane_live = (cb >= 0) && (cb < ld);
-    const bool lane_owned = lane_live && (lane * C >= Hx) && (lane * C < Hx + Wv);
+    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
+    // up to three that share a wider lane vector with the last column are written (as 0).
+    const bool lane_live = (cb >= 0) && (cb < nx);
+    const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane * C >= Hx) && (lane * C < Hx + Wv);
     T colm[C];  // 1 on interior columns, 0 on the boundary ring / padding
 #pragma unroll
     for (int c = 0; c < C; ++c) colm[c] = ((cb + c >= 1) && (cb + c <= nx - 2)) ? T(1) : T(0);

@@ -71,8 +71,10 @@ __global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArg
     const int strip = tile % strips;
     const int seg = tile / strips;
     const int cb = strip * kTileCols - kTileHalo + lane;  // grid column of this lane
-    const bool lane_live = (cb >= 0) && (cb < ld);
-    const bool lane_owned = lane_live && (lane >= kTileHalo) && (lane < kTileHalo + kTileCols);
+    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
+    // up to three that share a wider lane vector with the last column are written (as 0).
+    const bool lane_live = (cb >= 0) && (cb < nx);
+    const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane >= kTileHalo) && (lane < kTileHalo + kTileCols);
     const T colm = ((cb >= 1) && (cb <= nx - 2)) ? T(1) : T(0);
     const int r0 = seg * seg_rows;
     const int r1 = min(r0 + seg_rows, ny);
