@@ -262,10 +262,13 @@ enum {
     FDW_CFG_SMALL_TILES = 14,     /* small-grid kernel: one workgroup per tile of 48 owned columns,
                                      its waves advancing the tile level by level together.  0 (default):
                                      used where every member has at most 1024 x 1024 nodes; 1: never;
-                                     2: wherever allowed.  Never with receiver traces or the persistent
-                                     launch (the streaming kernel runs those steps).  States are
-                                     identical bit for bit; energies agree to rounding (other partial
-                                     sums) */
+                                     2: wherever allowed.  Never with the persistent launch (the streaming
+                                     kernel runs those steps).  States and traces are identical bit for
+                                     bit; energies agree to rounding (other partial sums).  The reverse
+                                     sweep of fdw_adjoint has such a kernel too (up to 8 reverse steps per
+                                     launch): it runs where this key allows it, unless the caller set one
+                                     of the FDW_CFG_ADJ_* keys to a value of its own or receivers share a
+                                     node; gradients agree to rounding */
     FDW_CFG_TILE_ROWS = 15        /* rows per tile of the small-grid kernel (16 halo rows included):
                                      32, 48 or 64 (0 = automatic: 64 where that gives a launch 150 to
                                      300 tiles, else 48 where that gives at least 150, else 32) */
@@ -295,7 +298,8 @@ int fdw_autotune(fdw_ctx* ctx, int32_t steps, int64_t* best_out);
  * arguments (as for fdw_adjoint; the gradient goes to grad_scratch, device double [ny][nx], and
  * the forward state is left unchanged) for each candidate (reverse time block, columns per lane,
  * rows per work item) and applies the fastest.  With checkpoints recorded by the forward run in
- * adj_ws the candidates time the reverse sweep alone.  Cached like fdw_autotune.  best_out (host,
+ * adj_ws the candidates time the reverse sweep alone.  The search times the streaming sweep only (as
+ * fdw_autotune; where the small-grid tiles run they keep running).  Cached like fdw_autotune.  best_out (host,
  * may be NULL) receives {adj_time_block, adj_segment_rows (0 = automatic), adj_lane_columns}. */
 int fdw_autotune_adjoint(fdw_ctx* ctx, int32_t member, const int32_t* recv_ij, int32_t R, const double* trace_grad,
                          int32_t ckpt_every, void* adj_ws, size_t adj_ws_bytes, double* grad_scratch,

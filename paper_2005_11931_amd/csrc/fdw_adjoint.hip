@@ -464,28 +464,31 @@ int adjoint_resident_waves<double>(int K, int C, bool face, bool split)
     return 0;
 }
 
-// lam^N = mu^N = s_N at the receivers (planes already zero).
+// lam^N = mu^N = s_N at the receivers (planes already zero): one thread per receiver of the list
+// sorted by (row, column, index); the first receiver of a node adds up the node's run in order.
 template <typename T>
-__global__ void k_adjoint_seed(T* lam, T* mu, int ld, const int* rec_ij, int R, const double* tg)
+__global__ __launch_bounds__(256) void k_adjoint_seed(T* lam, T* mu, int ld, const int* __restrict__ rec_ij,
+                                                      const int* __restrict__ id, int R, const double* __restrict__ tg)
 {
-    // one thread scatters all receivers in order so that coincident receivers add up
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        for (int r = 0; r < R; ++r) {
-            const size_t k = (size_t)rec_ij[2 * r + 1] * ld + rec_ij[2 * r];
-            lam[k] += (T)tg[r];
-            mu[k] += (T)tg[r];
-        }
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= R) return;
+    auto node = [&](int q) { return (size_t)rec_ij[2 * id[q] + 1] * ld + rec_ij[2 * id[q]]; };
+    const size_t at = node(k);
+    if (k > 0 && node(k - 1) == at) return;
+    T s = T(0);
+    for (int q = k; q < R && node(q) == at; ++q) s += (T)tg[id[q]];
+    lam[at] = s;
+    mu[at] = s;
 }
 template <typename T>
-hipError_t launch_adjoint_seed(const AdjArgs& a, int64_t N, hipStream_t s)
+hipError_t launch_adjoint_seed(const AdjArgs& a, const int* rec_ij, int64_t N, hipStream_t s)
 {
-    // rec_rowptr is unused here; rec_col holds the raw (i, j) pairs in this call
-    hipLaunchKernelGGL((k_adjoint_seed<T>), dim3(1), dim3(64), 0, s, (T*)a.lout, (T*)a.mout, a.ld, a.rec_col, a.R,
-                       a.trace_grad + N * a.R);
+    hipLaunchKernelGGL((k_adjoint_seed<T>), dim3((a.R + 255) / 256), dim3(256), 0, s, (T*)a.lout, (T*)a.mout, a.ld,
+                       rec_ij, a.rec_id, a.R, a.trace_grad + N * a.R);
     return hipGetLastError();
 }
-template hipError_t launch_adjoint_seed<float>(const AdjArgs&, int64_t, hipStream_t);
-template hipError_t launch_adjoint_seed<double>(const AdjArgs&, int64_t, hipStream_t);
+template hipError_t launch_adjoint_seed<float>(const AdjArgs&, const int*, int64_t, hipStream_t);
+template hipError_t launch_adjoint_seed<double>(const AdjArgs&, const int*, int64_t, hipStream_t);
 
 __global__ void k_grad_out(const double* __restrict__ g, int ld, int nx, int ny, double* __restrict__ out)
 {

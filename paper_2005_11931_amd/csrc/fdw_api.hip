@@ -99,6 +99,7 @@ struct fdw_ctx {
     int C = 4;  // columns per lane of the streaming kernels
     int adjK = 2, adjC = 2;  // time block and columns per lane of the reverse sweep
     int adjS_cfg = 0;        // rows per reverse work item (0 = automatic)
+    unsigned adj_set = 0;    // bits: reverse time block, lane columns, item rows set by the caller
     // checkpoints of the adjoint stored by the forward run of one member (member < 0: off)
     struct {
         int member = -1;
@@ -533,7 +534,6 @@ int launch_block(fdw_ctx* c, int first, int nm, int K, bool energy, bool trace, 
     int face_mode = c->m[first].face;
     for (int i = first; i < first + nm; ++i)
         if (c->m[i].face != face_mode) face_mode = -1;
-    if (c->tiles_now && trace) return fail(c, FDW_ENOTSUP, "tile decomposition with receiver traces");
     auto launch = [&](const StepArgs& sa, int face, int grid) {
         return c->tiles_now ? launch_step_tile<T>(sa, K, face, tile_rows(c) / kTileRowsPerWave, grid, s)
                             : launch_step<T>(sa, K, c->C, face, grid, s);
@@ -773,14 +773,14 @@ void replay_bookkeeping(fdw_ctx* c, int64_t steps, bool persistent)
     }
 }
 
-// Whether a step_n call runs the small-grid tile kernel: not with receiver traces (the streaming
-// kernel records them) or the persistent launch; automatically where every member has at most
+// Whether a step_n call runs the small-grid tile kernel: not with the persistent launch;
+// automatically where every member has at most
 // kTileAutoNodes nodes (there the streaming kernel's few, long work items leave much of the
 // device idle: measured faster from 256^2 to 1024^2 - at 1024^2 by 7% in FP64, 14% in FP32).
 constexpr int64_t kTileAutoNodes = (int64_t)1024 * 1024;
 bool want_tiles(const fdw_ctx* c)
 {
-    if (c->tile_mode == 1 || c->batch_mode == 1 || any_trace(c)) return false;
+    if (c->tile_mode == 1 || c->batch_mode == 1) return false;
     if (c->tile_mode == 2) return true;
     for (const HostMember& hm : c->m)
         if ((int64_t)hm.nx * hm.ny > kTileAutoNodes) return false;
@@ -1430,6 +1430,7 @@ int fdw_configure(fdw_ctx* c, int32_t key, int64_t v)
         }
         return FDW_OK;
     }
+    const bool set = v != 0;  // (a value of the caller's own, not the default)
     switch (key) {
     case FDW_CFG_TIME_BLOCK:
         if (v < 0 || v > kMaxTimeBlock || (c->dtype == FDW_F64 && c->C == 2 && v > 4) || (c->C == 4 && v > 6))
@@ -1469,6 +1470,7 @@ int fdw_configure(fdw_ctx* c, int32_t key, int64_t v)
             return fail(c, FDW_EINVAL, "adjoint time block must be 1..6 (double with 1 column per lane, float with 2) "
                                        "or 1..4");
         c->adjK = (int)v;
+        c->adj_set = (c->adj_set & ~1u) | (set ? 1u : 0u);
         break;
     case FDW_CFG_ADJ_LANE_COLUMNS:
         if (v == 0) v = (c->dtype == FDW_F64) ? 1 : 2;
@@ -1477,10 +1479,12 @@ int fdw_configure(fdw_ctx* c, int32_t key, int64_t v)
         if (c->adjK > 4 && !adj_narrow(c->dtype, (int)v))
             return fail(c, FDW_EINVAL, "adjoint time blocks above 4 need 1 (double) or 2 (float) columns per lane");
         c->adjC = (int)v;
+        c->adj_set = (c->adj_set & ~2u) | (set ? 2u : 0u);
         break;
     case FDW_CFG_ADJ_SEGMENT_ROWS:
         if (v != 0 && (v < kMinAdjSegRows || v > 4096)) return fail(c, FDW_EINVAL, "adjoint segment rows must be 0 or 16..4096");
         c->adjS_cfg = (int)v;
+        c->adj_set = (c->adj_set & ~4u) | (set ? 4u : 0u);
         break;
     case FDW_CFG_CHECK_ENERGY:
         if (v != 0 && v != 1) return fail(c, FDW_EINVAL, "check_energy must be 0 or 1");
@@ -1614,6 +1618,49 @@ int choose_adj_S(const fdw_ctx* c, const HostMember& hm, int K, bool split)
     return S0;
 }
 
+// Whether the reverse sweep of a member runs the small-grid tile kernel: automatically up to 1.25e6
+// nodes in FP64 and 2.6e6 in FP32 (gradient with 256 steps: 384^2 FP64 0.85 ms against 2.38 with the
+// streaming sweep, 1024^2 2.29 against 2.66, 1200^2 even; FP32 1024^2 1.75 against 3.14, 1801 x 1403
+// 3.33 against 3.49, 2048^2 4.67 against 3.94); not where the caller set the streaming sweep's own
+// parameters, and not with coincident receivers (`dups`: the tile kernel takes one source per
+// node).
+bool want_adj_tiles(const fdw_ctx* c, const HostMember& hm, int dups)
+{
+    if (c->tile_mode == 1 || c->adj_set || dups > 0) return false;
+    return c->tile_mode == 2 || (double)hm.nx * hm.ny <= (c->dtype == FDW_F32 ? 2.6e6 : 1.25e6);
+}
+
+// Rows and rows per wave of the reverse tiles: as in the forward tile kernel (tile_rows) 64 rows
+// where that gives 150 to 300 tiles (about one per CU), else 48 where that gives at least 150, else
+// 32.  Beyond 300 tiles of 64 rows the halo work decides in FP64 (64 rows: 1024^2 2.29 ms against 2.42
+// with 48, 2.85 with 32) and the waves per SIMD in FP32 (32 rows: 1801 x 1403 3.33 ms against 3.53
+// with 64, 3.63 with 48).  64-row tiles have 8 waves of 8 rows (700^2 FP64 1.29 ms; 12 waves of 4: 1.50).
+void adj_tile_shape(const fdw_ctx* c, const HostMember& hm, int* waves, int* rows_per_wave)
+{
+    auto tiles_of = [&](int rows) {
+        const int own = rows - 2 * kTileHalo;
+        return (int64_t)((hm.nx + kTileCols - 1) / kTileCols) * ((hm.ny + own - 1) / own);
+    };
+    int rows = c->tile_rows;
+    if (rows == 0) {
+        const int64_t t64 = tiles_of(64);
+        if (t64 > 300)
+            rows = c->dtype == FDW_F64 ? 64 : 32;
+        else
+            rows = t64 >= 150 ? 64 : tiles_of(48) >= 150 ? 48 : 32;
+    }
+    *rows_per_wave = rows == 64 ? 8 : 4;
+    *waves = rows / *rows_per_wave;
+}
+
+void adj_decompose_tile(const HostMember& hm, int rows, AdjArgs& a)
+{
+    a.seg_rows = rows - 2 * kTileHalo;
+    a.segs = (hm.ny + a.seg_rows - 1) / a.seg_rows;
+    a.strips = (hm.nx + kTileCols - 1) / kTileCols;
+    a.waves = a.strips * a.segs;
+}
+
 template <typename T>
 int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double* tg, int ck, void* ws, size_t wsb,
                  double* g1_out, double* g2_out)
@@ -1643,13 +1690,13 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
 
     // zero the reverse state planes (boundary ring and padding must be 0) and the accumulators
     HIPCHK(c, launch_fill_bytes(P.planes_begin, 8 * L.plane + 2 * L.plane64, s));
+    int st[2] = {0, 0};
     if (R > 0) {
         HIPCHK(c, hipMemcpyAsync(rec, recv_ij, sizeof(int) * 2 * (size_t)R, hipMemcpyDeviceToDevice, s));
         HIPCHK(c, launch_receivers_csr(rec, R, hm.nx, hm.ny, rowptr, rcol, rid, status, s));
-        int st = -1;
-        HIPCHK(c, hipMemcpyAsync(&st, status, sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipMemcpyAsync(st, status, sizeof(st), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
-        if (st != 0) return fail(c, FDW_EINVAL, "receivers must be interior nodes (1 <= i <= nx-2, 1 <= j <= ny-2)");
+        if (st[0] != 0) return fail(c, FDW_EINVAL, "receivers must be interior nodes (1 <= i <= nx-2, 1 <= j <= ny-2)");
     }
     if (N == 0) {
         HIPCHK(c, launch_grad_out(G1, hm.ld, hm.nx, hm.ny, g1_out, s));
@@ -1678,6 +1725,7 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
         HIPCHK(c, launch_start<T>(&rep, hm.u0, hm.u1, (T)hm.tau, 0, nullptr, c->red, s));
         int64_t n = 1;
         const int Kf = choose_K(c);
+        const bool replay_tiles = want_tiles(c);  // (both kernels give the same states bit for bit)
         int laidK = -1;
         auto store_ckpt = [&](int64_t step) -> int {
             const int64_t k = step / ck - 1;
@@ -1691,7 +1739,10 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
             const int64_t next = std::min<int64_t>(N, (n / ck + 1) * ck);
             const int Kb = (int)std::min<int64_t>(Kf, next - n);
             if (Kb != laidK) {
-                decompose(c, hm, rep, c->S_eff, Kb);
+                if (replay_tiles)
+                    decompose_tile(c, hm, rep);
+                else
+                    decompose(c, hm, rep, c->S_eff, Kb);
                 laidK = Kb;
             }
             StepArgs a;
@@ -1708,7 +1759,10 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
             a.ctx_step = 0;
             a.stream_nt = rep.stream_nt;
             a.reverse = 0;
-            HIPCHK(c, launch_step<T>(a, Kb, c->C, hm.face, rep.blocks, s));
+            if (replay_tiles)
+                HIPCHK(c, launch_step_tile<T>(a, Kb, hm.face, tile_rows(c) / kTileRowsPerWave, rep.blocks, s));
+            else
+                HIPCHK(c, launch_step<T>(a, Kb, c->C, hm.face, rep.blocks, s));
             cur ^= 1;
             n += Kb;
             if (n % ck == 0 && n < N) {
@@ -1741,17 +1795,19 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
     // seed lam^N = mu^N = s_N (planes are zero)
     A.lout = LA[0];
     A.mout = MU[0];
-    A.rec_col = rec;
-    if (R > 0) HIPCHK(c, launch_adjoint_seed<T>(A, N, s));
     A.rec_rowptr = rowptr;
     A.rec_col = rcol;
     A.rec_id = rid;
+    if (R > 0) HIPCHK(c, launch_adjoint_seed<T>(A, rec, N, s));
     const void* fu_in = top_u;
     const void* fd_in = top_d;
     int fcur = recorded ? 1 : cur;  // the first reverse output goes to the other state plane
     int lcur = 0;
-    const int Kr = adjoint_K(c);
-    const int Sr = choose_adj_S<T>(c, hm, Kr, g2_out != nullptr);
+    const bool tiles = want_adj_tiles(c, hm, st[1]);
+    int tile_waves = 0, tile_rw = 0;
+    adj_tile_shape(c, hm, &tile_waves, &tile_rw);
+    const int Kr = tiles ? kTileHalo : adjoint_K(c);
+    const int Sr = tiles ? 0 : choose_adj_S<T>(c, hm, Kr, g2_out != nullptr);
     int64_t mtop = N;
     while (mtop > 0) {
         if (mtop < N && mtop % ck == 0) {
@@ -1762,7 +1818,10 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
         }
         const int64_t seg_bot = ((mtop - 1) / ck) * ck;
         const int Kb = (int)std::min<int64_t>(Kr, mtop - seg_bot);
-        adj_decompose(c, hm, Kb, Sr, A);
+        if (tiles)
+            adj_decompose_tile(hm, tile_waves * tile_rw, A);
+        else
+            adj_decompose(c, hm, Kb, Sr, A);
         const int outk = fcur ^ 1;
         A.uin = fu_in;
         A.din = fd_in;
@@ -1773,8 +1832,10 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
         A.lout = LA[lcur ^ 1];
         A.mout = MU[lcur ^ 1];
         A.n_top = mtop;
-        const int grid = (A.waves + kWavesPerBlock - 1) / kWavesPerBlock;
-        HIPCHK(c, launch_adjoint_block<T>(A, Kb, c->adjC, grid, s));
+        if (tiles)
+            HIPCHK(c, launch_adjoint_tile<T>(A, Kb, tile_rw, tile_waves, s));
+        else
+            HIPCHK(c, launch_adjoint_block<T>(A, Kb, c->adjC, (A.waves + kWavesPerBlock - 1) / kWavesPerBlock, s));
         fu_in = FU[outk];
         fd_in = FD[outk];
         fcur = outk;
@@ -2083,8 +2144,12 @@ extern "C" int fdw_autotune_adjoint(fdw_ctx* c, int32_t m, const int32_t* recv_i
                 std::vector<float> ts;
                 for (int rep = 0; rep < 2; ++rep) {
                     HIPCHK(c, hipEventRecord(e0, c->stream));
+                    // (the streaming sweep: the small-grid tiles have no such parameters)
+                    const int saveTiles = c->tile_mode;
+                    c->tile_mode = 1;
                     rc = fdw_adjoint(c, m, recv_ij, R, trace_grad, ckpt_every, adj_ws, adj_ws_bytes, grad_scratch,
                                      nullptr);
+                    c->tile_mode = saveTiles;
                     if (rc) {
                         c->adjK = saveK;
                         c->adjC = saveC;

