@@ -236,13 +236,15 @@ enum {
     FDW_CFG_LANE_COLUMNS = 6, /* grid columns per lane of the streaming kernels: 2 or 4 (float), 1 or 2
                                  (double); 0 = default */
     FDW_CFG_ADJ_TIME_BLOCK = 7,  /* reverse steps per launch of the adjoint sweep: 1..6 with 1 (double) or
-                                    2 (float) columns per lane, else 1..4 (0 = 6 with those lane
-                                    layouts, the defaults, else 4) */
+                                    2 (float) columns per lane, else 1..4 (0 = automatic: 6 with those
+                                    lane layouts, the defaults, else 4; double with 1 column then takes 8
+                                    steps per launch, reported as 6) */
     FDW_CFG_ADJ_LANE_COLUMNS = 8, /* columns per lane of the adjoint sweep: 2 or 4 (float), 1 or 2 (double);
                                      0 = default (2 for float, 1 for double) */
-    FDW_CFG_ADJ_SEGMENT_ROWS = 9, /* rows per work item of the adjoint sweep, 16..4096 (0 = automatic: 4 x the
-                                     reverse time block, at least 16; lengthened, up to 16 x the block,
-                                     until one launch's items fit in the waves the device holds at once) */
+    FDW_CFG_ADJ_SEGMENT_ROWS = 9, /* rows per work item of the adjoint sweep, 16..4096 (0 = automatic: the
+                                     fewest that let one launch's items fit in the waves the device
+                                     holds at once, up to 16 (float) or 6 (double) x the reverse time
+                                     block; 4 or 6 x the block where none does) */
     FDW_CFG_CHECK_ENERGY = 10,    /* 1 (default): fdw_step_n checks the energies it computes and returns
                                      FDW_EUNSTABLE on a non-finite one or on growth beyond 10x the call's
                                      first energy (one word read back: such calls synchronise the stream);

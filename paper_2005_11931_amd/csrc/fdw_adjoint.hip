@@ -18,8 +18,8 @@
 // recurrence, u^n = u^{n+1} - du^{n+1}, du^n = du^{n+1} - L u^n, re-anchored at exact
 // checkpoints stored by the forward replay.  One launch advances K reverse levels with the
 // streaming structure of the forward kernel (one wave per strip x segment, K-column halo,
-// rows in registers, DPP lane exchange); the gradient of a node collects the K levels in
-// registers and is added to the FP64 accumulator plane once per launch.
+// rows in registers, DPP lane exchange); the face products collect the K levels in registers, and a
+// node's gradient is added to the FP64 accumulator plane once per launch.
 #include "fdw_internal.h"
 #include "fdw_stream.h"
 
@@ -42,8 +42,8 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     constexpr int Hx = ((K + C - 1) / C) * C;
     constexpr int Wv = kWaveSize * C - 2 * Hx;
     // rows are loaded NB - 1 rows ahead: two rows for FP64 with one column per lane and K a
-    // multiple of 3 (the default reverse configuration, which stays at two waves per SIMD),
-    // one row elsewhere (a deeper prefetch would push the FP32 variants to one wave)
+    // multiple of 3, one row elsewhere (a deeper prefetch would push FP32 at K = 6 and FP64 at
+    // K = 8 to one wave per SIMD)
     constexpr int NB = (sizeof(T) == 8 && C == 1 && K % 3 == 0) ? 3 : 2;
     constexpr int U = (K % 2 == 0) ? K : 2 * K;
     static_assert(U % NB == 0 && U % K == 0 && U % 2 == 0, "row unroll");
@@ -115,8 +115,9 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     T Mr[K][2][C];      // mu^{m-s}
     T Gu[K][C];         // y flux of u^{m-s} below row r (level s stores at s-1)
     T Gl[K][C];         // y flux of lam^{m-s+1} below row r
-    double Py[K][C];    // y face products below row r
-    double GX[K][C], GY[K][C];  // gradient of rows p-1 .. p-K (by position modulo K); GY only if SPLIT
+    double SX[K][C], SY[K][C];  // face sums of rows p-1 .. p-K (by position modulo K): the x faces right
+                                // of the row's nodes, the y faces to the next row in the stream
+    double Slast[C];            // SY of the row that completed last
     double gbuf[NB][C], g2buf[NB][C];  // accumulator rows, loaded NB - 1 iterations ahead
     T FXr[K][C], FYr[K][C];
     T hprev[C], hyprev[C];
@@ -134,10 +135,11 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
         for (int t = 0; t < K; ++t) {
             Dr[t][0][c] = Dr[t][1][c] = Lr[t][0][c] = Lr[t][1][c] = Mr[t][0][c] = Mr[t][1][c] = T(0);
             Gu[t][c] = Gl[t][c] = T(0);
-            Py[t][c] = GX[t][c] = GY[t][c] = 0.0;
+            SX[t][c] = SY[t][c] = 0.0;
             FXr[t][c] = FYr[t][c] = T(0);
         }
         hprev[c] = hyprev[c] = T(0);
+        Slast[c] = 0.0;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             bu[q][c] = bd[q][c] = bl[q][c] = bm[q][c] = bh[q][c] = bhy[q][c] = T(0);
@@ -171,6 +173,14 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     }
     const int nblk = (r1 - r0 + 2 * K + U - 1) / U;
 
+    // FP32: two copies of the row loop.  Items that stay clear of the grid's first and last rows and
+    // whose rows hold no receiver (nearly all) run one without the tests for either: a test per
+    // level splits the row into pieces that the instruction scheduler cannot look across, and with
+    // one or two waves per SIMD nothing else fills the gaps of each level's dependent chain (1801 x 1403,
+    // 16-row items: 8.0 -> 7.4 us per reverse step).  FP64 waits for memory instead, and a second copy
+    // costs it registers (2048^2, K = 8: 14.7 us per step with one, 17.4 with two).
+    auto rows = [&](auto general) {
+    constexpr bool GENERAL = decltype(general)::value;
     for (int blk = 0; blk < nblk; ++blk) {
 #pragma unroll
         for (int s = 0; s < U; ++s) {
@@ -222,10 +232,9 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                 const int pr = pmod(s - t, 2);
                 const int pr1 = pmod(s - t + 1, 2);
                 const int q = pmod(s - t, K);
-                const bool rin = (r >= 1) && (r <= ny - 2);
+                const bool rin = !GENERAL || ((r >= 1) && (r <= ny - 2));
                 const bool rown = (r >= r0) && (r < r1);
                 const int64_t n = a.n_top - t;  // time of this level's forward state
-                const double w = (n == 0) ? 0.5 : 1.0;
                 // u^{m-t}(r+1) = u^{m-t+1}(r+1) - du^{m-t+1}(r+1); u and du are zero on the
                 // Dirichlet rows at every level (and rows outside the grid load as zero), so
                 // this needs no row test
@@ -234,55 +243,53 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                 // x fluxes and face differences of u^{m-t} and lam^{m-t+1} at row r
                 const T uR = lane_from_right(Ur[t][pr][0]);
                 const T lR = lane_from_right(Lr[t - 1][pr][0]);
-                T Fu[C], Fl[C];
-                double Px[C];
+                T Fu[C], Fl[C], dux[C], dlx[C], duy[C], dly[C];
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    const T du = ((c < C - 1) ? Ur[t][pr][c + 1] : uR) - Ur[t][pr][c];
-                    const T dl = ((c < C - 1) ? Lr[t - 1][pr][c + 1] : lR) - Lr[t - 1][pr][c];
-                    Fu[c] = FXr[q][c] * du;
-                    Fl[c] = FXr[q][c] * dl;
-                    Px[c] = (double)du * (double)dl;
+                    dux[c] = ((c < C - 1) ? Ur[t][pr][c + 1] : uR) - Ur[t][pr][c];
+                    dlx[c] = ((c < C - 1) ? Lr[t - 1][pr][c + 1] : lR) - Lr[t - 1][pr][c];
+                    duy[c] = Ur[t][pr1][c] - Ur[t][pr][c];
+                    dly[c] = Lr[t - 1][pr1][c] - Lr[t - 1][pr][c];
+                    Fu[c] = FXr[q][c] * dux[c];
+                    Fl[c] = FXr[q][c] * dlx[c];
                 }
                 const T FuL = lane_from_left(Fu[C - 1]);
                 const T FlL = lane_from_left(Fl[C - 1]);
-                const double PxL = lane_from_left(Px[C - 1]);
                 T nd[C], nm[C], nl[C];
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    const T duy = Ur[t][pr1][c] - Ur[t][pr][c];
-                    const T dly = Lr[t - 1][pr1][c] - Lr[t - 1][pr][c];
-                    const T Gun = FYr[q][c] * duy;
-                    const T Gln = FYr[q][c] * dly;
-                    const double Pyn = (double)duy * (double)dly;
+                    const T Gun = FYr[q][c] * duy[c];
+                    const T Gln = FYr[q][c] * dly[c];
                     const T Lu = (Fu[c] - ((c > 0) ? Fu[c - 1] : FuL)) + (Gun - Gu[t - 1][c]);
                     const T Ll = (Fl[c] - ((c > 0) ? Fl[c - 1] : FlL)) + (Gln - Gl[t - 1][c]);
                     Gu[t - 1][c] = Gun;
                     Gl[t - 1][c] = Gln;
-                    const double gx = Px[c] + ((c > 0) ? Px[c - 1] : PxL);
-                    const double gy = Pyn + Py[t - 1][c];
-                    Py[t - 1][c] = Pyn;
-                    GX[q][c] = __builtin_fma(-w * axd, gx, GX[q][c]);
-                    if (split)
-                        GY[q][c] = __builtin_fma(-w * ayd, gy, GY[q][c]);
-                    else
-                        GX[q][c] = __builtin_fma(-w * ayd, gy, GX[q][c]);
-                    // pin the accumulation here: it is consumed only when the row completes,
-                    // and left alone the compiler may defer it there, keeping face products
-                    // of several rows alive
-                    asm volatile("" : "+v"(GX[q][c]));
-                    if (split) asm volatile("" : "+v"(GY[q][c]));
                     nd[c] = fma_t(-Lu, colm[c], Dr[t - 1][pr][c]);
                     nm[c] = fma_t(Ll, colm[c], Mr[t - 1][pr][c]);
                 }
+                // the start step's term (n = 0, the last level of the last launch) counts half
+                if (t == K && __builtin_expect(n == 0, 0)) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) dlx[c] *= T(0.5), dly[c] *= T(0.5);
+                    asm volatile("");
+                }
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    SX[q][c] = __builtin_fma((double)dux[c], (double)dlx[c], SX[q][c]);
+                    SY[q][c] = __builtin_fma((double)duy[c], (double)dly[c], SY[q][c]);
+                    // pin the accumulation here: it is consumed only when the row completes, and
+                    // left alone the compiler may defer it there, keeping face differences of
+                    // several rows alive
+                    asm volatile("" : "+v"(SX[q][c]), "+v"(SY[q][c]));
+                }
                 // Dirichlet rows keep du = mu = 0 (and with them u = lam = 0); the row test is
                 // wave-uniform, and the empty asm keeps it a scalar branch instead of selects
-                if (__builtin_expect(!rin, 0)) {
+                if (GENERAL && __builtin_expect(!rin, 0)) {
 #pragma unroll
                     for (int c = 0; c < C; ++c) nd[c] = nm[c] = T(0);
                     asm volatile("");
                 }
-                if (t == 1 && __builtin_expect(any_rec, 0)) {
+                if (GENERAL && t == 1 && __builtin_expect(any_rec, 0)) {
                     // receivers of row r in the columns this strip computes (halo included:
                     // every copy of a node takes its source), once per row
                     int kb = 0, ke = 0;
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                     RPb[q] = kb;
                     RPe[q] = ke;
                 }
-                if (__builtin_expect(any_rec && rin && RPb[q] < RPe[q], 0)) {
+                if (GENERAL && __builtin_expect(any_rec && rin && RPb[q] < RPe[q], 0)) {
                     const int kb = RPb[q], ke = RPe[q];
                     for (int k = kb; k < ke; ++k) {
                         const int off = rcol[k] - cb;
@@ -336,17 +343,25 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                     }
                 }
             }
-            // the row at position p-K has all K contributions (ring index (p-K) mod K = s mod K)
+            // the row at position p-K has all K contributions (ring index (p-K) mod K = s mod K): its
+            // nodes take the sums of their two x faces and of the y faces on both sides
             {
                 const int qd = pmod(s, K);
                 const int r = rfirst + dir * (p - K);
+                const double SL = lane_from_left(SX[qd][C - 1]);
                 if (r >= r0 && r < r1 && lane_owned) {
                     const size_t off = (size_t)(ptrdiff_t)r * ld + (size_t)(ptrdiff_t)cb;
                     double o1[C], o2[C];
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        o1[c] = gbuf[pb][c] + GX[qd][c];
-                        o2[c] = g2buf[pb][c] + GY[qd][c];
+                        const double gx = SX[qd][c] + ((c > 0) ? SX[qd][c - 1] : SL);
+                        const double gy = SY[qd][c] + Slast[c];
+                        if (split) {
+                            o1[c] = __builtin_fma(-axd, gx, gbuf[pb][c]);
+                            o2[c] = __builtin_fma(-ayd, gy, g2buf[pb][c]);
+                        } else {
+                            o1[c] = gbuf[pb][c] + __builtin_fma(-ayd, gy, -axd * gx);
+                        }
                     }
                     if (a.stream_nt) {
                         store_row_nt<double, C>(a.g1 + off, o1);
@@ -357,11 +372,20 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                     }
                 }
 #pragma unroll
-                for (int c = 0; c < C; ++c) GX[qd][c] = GY[qd][c] = 0.0;
+                for (int c = 0; c < C; ++c) {
+                    Slast[c] = SY[qd][c];
+                    SX[qd][c] = SY[qd][c] = 0.0;
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    };
+    // (rows streamed past the item's halo, to fill the last unrolled block, influence nothing)
+    if (sizeof(T) == 8 || any_rec || r0 - K < 1 || r1 + K - 1 > ny - 2)
+        rows(BoolTag<true>{});
+    else
+        rows(BoolTag<false>{});
 }
 
 template <typename T, int K, int C>
@@ -380,7 +404,8 @@ static hipError_t adj_launch_kc(const AdjArgs& a, int grid, hipStream_t s)
     return hipGetLastError();
 }
 
-// reverse time blocks 1..KMAX of one (T, C) configuration
+// reverse time blocks 1..KMAX of one (T, C) configuration, 7 excepted (its row loop, unrolled 14
+// times, does not fit the registers: the sweep takes 4 + 3 there)
 template <typename T, int C, int KMAX>
 static hipError_t adj_launch_c(const AdjArgs& a, int K, int grid, hipStream_t s)
 {
@@ -391,12 +416,13 @@ static hipError_t adj_launch_c(const AdjArgs& a, int K, int grid, hipStream_t s)
     case 4: return adj_launch_kc<T, 4, C>(a, grid, s);
     case 5: return KMAX >= 5 ? adj_launch_kc<T, (KMAX >= 5 ? 5 : 1), C>(a, grid, s) : hipErrorInvalidValue;
     case 6: return KMAX >= 6 ? adj_launch_kc<T, (KMAX >= 6 ? 6 : 1), C>(a, grid, s) : hipErrorInvalidValue;
+    case 8: return KMAX >= 8 ? adj_launch_kc<T, (KMAX >= 8 ? 8 : 1), C>(a, grid, s) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 }
 
-// One 8-byte value per lane and row (FP32 pairs, FP64 singles) goes up to 6 reverse steps per
-// launch at two waves per SIMD; the wider configurations to 4.
+// One 8-byte value per lane and row goes up to 6 reverse steps per launch (FP32 pairs) or 8 (FP64
+// singles) at two waves per SIMD; the wider configurations to 4.
 template <>
 hipError_t launch_adjoint_block<float>(const AdjArgs& a, int K, int C, int grid, hipStream_t s)
 {
@@ -407,7 +433,7 @@ hipError_t launch_adjoint_block<float>(const AdjArgs& a, int K, int C, int grid,
 template <>
 hipError_t launch_adjoint_block<double>(const AdjArgs& a, int K, int C, int grid, hipStream_t s)
 {
-    if (C == 1) return adj_launch_c<double, 1, 6>(a, K, grid, s);
+    if (C == 1) return adj_launch_c<double, 1, 8>(a, K, grid, s);
     if (C == 2) return adj_launch_c<double, 2, 4>(a, K, grid, s);
     return hipErrorInvalidValue;
 }
@@ -445,6 +471,7 @@ static int adj_resident_c(int K, bool face, bool split)
     case 4: return adj_resident_kc<T, 4, C>(face, split);
     case 5: return KMAX >= 5 ? adj_resident_kc<T, (KMAX >= 5 ? 5 : 1), C>(face, split) : 0;
     case 6: return KMAX >= 6 ? adj_resident_kc<T, (KMAX >= 6 ? 6 : 1), C>(face, split) : 0;
+    case 8: return KMAX >= 8 ? adj_resident_kc<T, (KMAX >= 8 ? 8 : 1), C>(face, split) : 0;
     default: return 0;
     }
 }
@@ -459,7 +486,7 @@ int adjoint_resident_waves<float>(int K, int C, bool face, bool split)
 template <>
 int adjoint_resident_waves<double>(int K, int C, bool face, bool split)
 {
-    if (C == 1) return adj_resident_c<double, 1, 6>(K, face, split);
+    if (C == 1) return adj_resident_c<double, 1, 8>(K, face, split);
     if (C == 2) return adj_resident_c<double, 2, 4>(K, face, split);
     return 0;
 }

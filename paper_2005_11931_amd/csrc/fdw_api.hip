@@ -1580,11 +1580,16 @@ int64_t fdw_get_config(const fdw_ctx* c, int32_t key)
 // =============================================================================================
 namespace {
 
-int adjoint_K(const fdw_ctx* c) { return c->adjK; }
+// Reverse steps per launch.  The automatic choice in double with one column per lane is 8 (reported
+// as 6, the largest block the caller can set): the sweep waits for memory there, and 8 levels move
+// 11 words per node 6 levels moved (2048^2: 16.9 -> 13.3 us per step, 4096^2: 63 -> 49).  In float 8 levels
+// need more than the 256 registers of two waves per SIMD (3000^2: 20.4 us per step with 6, 19 to 24 with 8).
+int adjoint_K(const fdw_ctx* c)
+{
+    const bool automatic = c->adjK == 6 && !(c->adj_set & 1u);
+    return automatic && c->dtype == FDW_F64 && c->adjC == 1 ? 8 : c->adjK;
+}
 
-// Rows per reverse work item: 4K, at least 16 (measured best at 2048^2: 16 rows at K = 4,
-// 24 at K = 6); short items keep many waves in flight for this register-heavy kernel, and the
-// 2K halo rows of an item are largely shared with its neighbours through L2.
 void adj_decompose(const fdw_ctx* c, const HostMember& hm, int K, int S, AdjArgs& a)
 {
     const int C = c->adjC;
@@ -1596,43 +1601,45 @@ void adj_decompose(const fdw_ctx* c, const HostMember& hm, int K, int S, AdjArgs
     a.waves = a.strips * a.segs;
 }
 
-// Rows per reverse work item.  The default is 4K (at least 16): every item recomputes 2K halo
-// rows, so shorter items waste more, longer ones leave fewer items to fill the device.  When
-// the 4K-row items of a small grid need a second round of resident waves (the reverse kernel
-// holds two per SIMD), that round is mostly idle and costs a whole item time; the items are
-// then lengthened, in steps of 8 rows up to 16K, until they fit in one round.
+// Rows per reverse work item: the fewest, from 16 in steps of 8, that give one launch no more items
+// than the waves the device holds at once (the reverse kernel holds two per SIMD).  Short items
+// keep every SIMD busy on grids of 1000 to 2000 nodes a side (1801 x 1403 FP32: 7.5 us per step with 16
+// rows, 9.0 with 24), and a second, mostly idle round costs a whole item time (2048^2 FP64: 13.3 us with
+// 48 rows in one round, 15.7 with 32, 15.0 with 24).  Items are lengthened up to 16K rows in float, 6K
+// in double; beyond, several rounds of 4K (float) or 6K rows (double: 2600^2 22.5 us, 26 with 64 rows).
 template <typename T>
 int choose_adj_S(const fdw_ctx* c, const HostMember& hm, int K, bool split)
 {
     if (c->adjS_cfg > 0) return c->adjS_cfg;
     const int cap = std::max(kMinAdjSegRows, (int)align_up((size_t)hm.ny, 8));
-    const int S0 = std::min(std::max(kMinAdjSegRows, (4 * K + 7) / 8 * 8), cap);
+    const bool f64 = c->dtype == FDW_F64;
+    const int many = std::min(std::max(kMinAdjSegRows, ((f64 ? 6 : 4) * K + 7) / 8 * 8), cap);
+    const int most = std::min(f64 ? 6 * K : 16 * K, cap);
     const int resident = adjoint_resident_waves<T>(K, c->adjC, hm.face != 0, split);
+    if (resident <= 0) return many;
     AdjArgs a;
-    adj_decompose(c, hm, K, S0, a);
-    if (resident <= 0 || a.waves <= resident) return S0;
-    for (int S = S0 + 8; S <= std::min(16 * K, cap); S += 8) {
+    for (int S = kMinAdjSegRows; S <= most; S += 8) {
         adj_decompose(c, hm, K, S, a);
         if (a.waves <= resident) return S;
     }
-    return S0;
+    return many;
 }
 
-// Whether the reverse sweep of a member runs the small-grid tile kernel: automatically up to 1.25e6
-// nodes in FP64 and 2.6e6 in FP32 (gradient with 256 steps: 384^2 FP64 0.85 ms against 2.38 with the
-// streaming sweep, 1024^2 2.29 against 2.66, 1200^2 even; FP32 1024^2 1.75 against 3.14, 1801 x 1403
-// 3.33 against 3.49, 2048^2 4.67 against 3.94); not where the caller set the streaming sweep's own
+// Whether the reverse sweep of a member runs the small-grid tile kernel: automatically up to 1024^2
+// nodes in FP64 and 2.1e6 in FP32 (gradient with 256 steps: 384^2 FP64 0.85 ms against 2.38 with the
+// streaming sweep, 1024^2 2.22 against 2.31, 1100^2 3.11 against 2.69; FP32 1024^2 1.73 against 2.62,
+// 1400^2 2.81 against 2.91, 1500^2 3.00 against 2.98, 1801 x 1403 3.29 against 2.98); not where the caller set the streaming sweep's own
 // parameters, and not with coincident receivers (`dups`: the tile kernel takes one source per
 // node).
 bool want_adj_tiles(const fdw_ctx* c, const HostMember& hm, int dups)
 {
     if (c->tile_mode == 1 || c->adj_set || dups > 0) return false;
-    return c->tile_mode == 2 || (double)hm.nx * hm.ny <= (c->dtype == FDW_F32 ? 2.6e6 : 1.25e6);
+    return c->tile_mode == 2 || (double)hm.nx * hm.ny <= (c->dtype == FDW_F32 ? 2.1e6 : 1.05e6);
 }
 
 // Rows and rows per wave of the reverse tiles: as in the forward tile kernel (tile_rows) 64 rows
 // where that gives 150 to 300 tiles (about one per CU), else 48 where that gives at least 150, else
-// 32.  Beyond 300 tiles of 64 rows the halo work decides in FP64 (64 rows: 1024^2 2.29 ms against 2.42
+// 32.  Beyond 300 tiles of 64 rows the halo work decides in FP64 (64 rows: 1024^2 2.22 ms against 2.42
 // with 48, 2.85 with 32) and the waves per SIMD in FP32 (32 rows: 1801 x 1403 3.33 ms against 3.53
 // with 64, 3.63 with 48).  64-row tiles have 8 waves of 8 rows (700^2 FP64 1.29 ms; 12 waves of 4: 1.50).
 void adj_tile_shape(const fdw_ctx* c, const HostMember& hm, int* waves, int* rows_per_wave)
@@ -1817,7 +1824,8 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
             fd_in = CD[k];
         }
         const int64_t seg_bot = ((mtop - 1) / ck) * ck;
-        const int Kb = (int)std::min<int64_t>(Kr, mtop - seg_bot);
+        int Kb = (int)std::min<int64_t>(Kr, mtop - seg_bot);
+        if (!tiles && Kb == 7) Kb = 4;  // (the streaming sweep has no blocks of 7)
         if (tiles)
             adj_decompose_tile(hm, tile_waves * tile_rw, A);
         else
