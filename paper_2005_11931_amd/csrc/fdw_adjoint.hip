@@ -517,21 +517,9 @@ hipError_t launch_adjoint_seed(const AdjArgs& a, const int* rec_ij, int64_t N, h
 template hipError_t launch_adjoint_seed<float>(const AdjArgs&, const int*, int64_t, hipStream_t);
 template hipError_t launch_adjoint_seed<double>(const AdjArgs&, const int*, int64_t, hipStream_t);
 
-__global__ void k_grad_out(const double* __restrict__ g, int ld, int nx, int ny, double* __restrict__ out)
-{
-    const int64_t total = (int64_t)nx * ny;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(k / nx), i = (int)(k % nx);
-        out[k] = g[(size_t)j * ld + i];
-    }
-}
 hipError_t launch_grad_out(const double* g, int ld, int nx, int ny, double* out, hipStream_t s)
 {
-    const int64_t total = (int64_t)nx * ny;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_grad_out, dim3(blocks), dim3(256), 0, s, g, ld, nx, ny, out);
-    return hipGetLastError();
+    return launch_copy_out<double>(g, ld, nx, ny, out, s);
 }
 
 }  // namespace fdw

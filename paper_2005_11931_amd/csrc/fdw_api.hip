@@ -37,6 +37,7 @@ inline size_t plane_alloc(int ld, int ny, size_t es)
 inline void* plane_origin(void* base, int ld, size_t es) { return (char*)base + (size_t)kPadRowsTop * ld * es; }
 inline size_t elem_size(int dtype) { return dtype == FDW_F32 ? 4 : 8; }
 inline int pitch_of(int nx) { return (int)align_up((size_t)nx, 64); }
+constexpr int64_t kOneLaunchNodes = (int64_t)1 << 20;  // states up to here are read out in one launch
 constexpr int kMinSegRows = 8;      // rows per streaming work item, at least
 constexpr int kMinAdjSegRows = 16;  // ... and per reverse-sweep work item
 
@@ -1337,16 +1338,18 @@ int fdw_get_state(fdw_ctx* c, int32_t m, void* u, void* du, int64_t* n)
     HostMember& hm = c->m[m];
     if (n) *n = hm.n;
     const void* su = (hm.n == 0) ? hm.u0 : hm.u[hm.cur];
+    const bool f32 = c->dtype == FDW_F32;
+    const void* sd = (hm.n == 0) ? nullptr : hm.d[hm.cur];
+    if (du && !sd)
+        HIPCHK(c, launch_fill_bytes(du, (size_t)hm.nx * hm.ny * elem_size(c->dtype), c->stream));
+    // small planes go in one launch (64^2: a launch costs more than both copies)
+    const bool both = u && du && sd && (int64_t)hm.nx * hm.ny <= kOneLaunchNodes;
     if (u)
-        HIPCHK(c, (c->dtype == FDW_F32) ? launch_copy_out<float>(su, hm.ld, hm.nx, hm.ny, u, c->stream)
-                                        : launch_copy_out<double>(su, hm.ld, hm.nx, hm.ny, u, c->stream));
-    if (du) {
-        if (hm.n == 0)
-            HIPCHK(c, launch_fill_bytes(du, (size_t)hm.nx * hm.ny * elem_size(c->dtype), c->stream));
-        else
-            HIPCHK(c, (c->dtype == FDW_F32) ? launch_copy_out<float>(hm.d[hm.cur], hm.ld, hm.nx, hm.ny, du, c->stream)
-                                            : launch_copy_out<double>(hm.d[hm.cur], hm.ld, hm.nx, hm.ny, du, c->stream));
-    }
+        HIPCHK(c, f32 ? launch_copy_out<float>(su, hm.ld, hm.nx, hm.ny, u, c->stream, both ? sd : nullptr, both ? du : nullptr)
+                      : launch_copy_out<double>(su, hm.ld, hm.nx, hm.ny, u, c->stream, both ? sd : nullptr, both ? du : nullptr));
+    if (du && sd && !both)
+        HIPCHK(c, f32 ? launch_copy_out<float>(sd, hm.ld, hm.nx, hm.ny, du, c->stream)
+                      : launch_copy_out<double>(sd, hm.ld, hm.nx, hm.ny, du, c->stream));
     return FDW_OK;
 }
 

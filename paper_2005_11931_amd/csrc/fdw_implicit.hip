@@ -599,25 +599,6 @@ __global__ __launch_bounds__(256) void k_adi_faces(const T* __restrict__ h1, con
         for (int q = 0; q < 4; ++q) red[4 * blockIdx.x + q] = s[q][0];
 }
 
-// dense [ny][nx] -> pitched [ny][ld], boundary ring zeroed
-template <typename T>
-__global__ void k_adi_copy_in(const T* __restrict__ src, int nx, int ny, int ld, T* __restrict__ dst)
-{
-    const int64_t total = (int64_t)ld * ny;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(k / ld), i = (int)(k % ld);
-        const bool in = i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2;
-        dst[k] = in ? src[(size_t)j * nx + i] : T(0);
-    }
-}
-template <typename T>
-__global__ void k_adi_copy_out(const T* __restrict__ src, int nx, int ny, int ld, T* __restrict__ dst)
-{
-    const int64_t total = (int64_t)nx * ny;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x)
-        dst[k] = src[(size_t)(k / nx) * ld + (k % nx)];
-}
-
 }  // namespace
 
 struct fdw_adi {
@@ -793,8 +774,8 @@ template <typename T>
 int adi_setup(fdw_adi* s, const void* u0, const void* u1, const void* h1, const void* h2)
 {
     const int nx = s->nx, ny = s->ny;
-    hipLaunchKernelGGL((k_adi_copy_in<T>), dim3(512), dim3(256), 0, s->stream, (const T*)u0, nx, ny, s->ld, (T*)s->u0);
-    hipLaunchKernelGGL((k_adi_copy_in<T>), dim3(512), dim3(256), 0, s->stream, (const T*)u1, nx, ny, s->ld, (T*)s->u1);
+    ADICHK(s, fdw::launch_copy_in<T>(u0, nx, ny, s->u0, s->ld, 1, s->stream));
+    ADICHK(s, fdw::launch_copy_in<T>(u1, nx, ny, s->u1, s->ld, 1, s->stream));
     hipLaunchKernelGGL((k_adi_faces<T>), dim3(kAdiRedBlocks), dim3(256), 0, s->stream, (const T*)h1,
                        (const T*)(h2 ? h2 : h1), nx, ny, s->ld, (T*)s->hx, (T*)s->hy, s->red);
     ADICHK(s, hipGetLastError());
@@ -931,27 +912,18 @@ int fdw_adi_get_state(fdw_adi* s, void* u, void* du, int64_t* n)
     if (n) *n = s->n;
     const bool f32 = s->p.dtype == FDW_F32;
     const void* su = (s->n == 0) ? s->u0 : s->u;
-    if (u) {
-        if (f32)
-            hipLaunchKernelGGL((k_adi_copy_out<float>), dim3(512), dim3(256), 0, s->stream, (const float*)su, s->nx,
-                               s->ny, s->ld, (float*)u);
-        else
-            hipLaunchKernelGGL((k_adi_copy_out<double>), dim3(512), dim3(256), 0, s->stream, (const double*)su, s->nx,
-                               s->ny, s->ld, (double*)u);
-        ADICHK(s, hipGetLastError());
-    }
-    if (du) {
-        if (s->n == 0) {
-            ADICHK(s, fdw::launch_fill_bytes(du, (size_t)s->nx * s->ny * (f32 ? 4 : 8), s->stream));
-        } else if (f32) {
-            hipLaunchKernelGGL((k_adi_copy_out<float>), dim3(512), dim3(256), 0, s->stream, (const float*)s->du, s->nx,
-                               s->ny, s->ld, (float*)du);
-        } else {
-            hipLaunchKernelGGL((k_adi_copy_out<double>), dim3(512), dim3(256), 0, s->stream, (const double*)s->du,
-                               s->nx, s->ny, s->ld, (double*)du);
-        }
-        ADICHK(s, hipGetLastError());
-    }
+    const void* sd = (s->n == 0) ? nullptr : s->du;
+    if (du && !sd) ADICHK(s, fdw::launch_fill_bytes(du, (size_t)s->nx * s->ny * (f32 ? 4 : 8), s->stream));
+    auto copy = [&](const void* a, void* to, const void* a1, void* to1) {
+        return f32 ? fdw::launch_copy_out<float>(a, s->ld, s->nx, s->ny, to, s->stream, a1, to1)
+                   : fdw::launch_copy_out<double>(a, s->ld, s->nx, s->ny, to, s->stream, a1, to1);
+    };
+    if (u && du && sd)
+        ADICHK(s, copy(su, u, sd, du));
+    else if (u)
+        ADICHK(s, copy(su, u, nullptr, nullptr));
+    else if (du && sd)
+        ADICHK(s, copy(sd, du, nullptr, nullptr));
     return FDW_OK;
 }
 

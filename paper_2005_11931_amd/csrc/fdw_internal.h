@@ -126,7 +126,8 @@ hipError_t launch_misfit(const void* traces, const double* d, int64_t n, double*
 template <typename T>
 hipError_t launch_copy_in(const void* src, int nx, int ny, void* dst, int ld, int zero_ring, hipStream_t s);
 template <typename T>
-hipError_t launch_copy_out(const void* src, int ld, int nx, int ny, void* dst, hipStream_t s);
+hipError_t launch_copy_out(const void* src, int ld, int nx, int ny, void* dst, hipStream_t s,
+                           const void* src1 = nullptr, void* dst1 = nullptr);  // (a second plane when dst1 is given)
 hipError_t launch_fill_bytes(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_set_int(int* p, int v, hipStream_t s);  // *p = v, stream-ordered (a kernel, not a memset)
 template <typename T>
