@@ -29,14 +29,6 @@ __device__ __forceinline__ double dpp_f64(double v)
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
-__device__ __forceinline__ double readlane_f64(double v, int l)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const unsigned int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
-    const unsigned int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 // MODE bit 0: per-step energy partials; bit 1: receiver traces.  FACE: coefficient layout as in
 // the streaming kernel.  The body of k_step_tile (MODE 0, 1) and k_record_tile (MODE 2, 3).
 template <typename T, int FACE, int MODE>
@@ -46,12 +38,13 @@ __device__ __forceinline__ void tile_block(const StepArgs& a, int K)
     constexpr bool want_trace = (MODE & 2) != 0;
     constexpr int RW = kTileRowsPerWave;
     __shared__ T s_edge[2][kMaxTileWaves][2][kWaveSize];  // first / last row of every wave, two levels
-    __shared__ double s_e[kMaxTimeBlock][kMaxTileWaves];  // energy partial of every wave and level
+    __shared__ double s_e[kMaxTimeBlock][4 * kMaxTileWaves];  // energy of every level and row of 16 lanes
 
     const int NW = (int)(blockDim.x >> 6);
     const int w = wave_in_block();
     const int lane = threadIdx.x & 63;
     const int gb = (int)blockIdx.x + a.block_offset;
+    const int eslot = a.eslot;
     const bool one = a.nmembers == 1;
     const int m = one ? a.first : find_member(a.table, a.first, a.nmembers, gb);
     const MemberDev M = member_copy(member_at(a.table, m, one, offsetof(StepArgs, one)));
@@ -157,6 +150,11 @@ __device__ __forceinline__ void tile_block(const StepArgs& a, int K)
     GlobalPtr<T> const trace_out = want_trace ? (GlobalPtr<T>)uniform_ptr((T*)M.traces) : nullptr;
     const int64_t trace_row0 = want_trace ? a.ctx_step + M.n_offset + 1 : 0;
 
+    // The halo rows are whole waves (kTileHalo is a multiple of the rows per wave), and rows past the
+    // grid hold zeros, which add nothing: a wave's energy terms count or not as a whole.  (A test
+    // per row was a branch in every row of every level.)
+    static_assert(kTileHalo % RW == 0, "halo rows are whole waves");
+    const bool wave_owned = w >= kTileHalo / RW && w < NW - kTileHalo / RW;
     // per-lane energy terms of every level, reduced over the wave once after the last level
     // (the K reductions are then independent and their lane exchanges overlap; reduced level
     // by level they would put six dependent exchanges into every level's critical path)
@@ -192,7 +190,7 @@ __device__ __forceinline__ void tile_block(const StepArgs& a, int K)
             T nd = fma_t(L, colm, d[i]);
             if (!((g >= 1) && (g <= ny - 2))) nd = T(0);  // Dirichlet rows (and rows outside the grid)
             const T nu = u[i] + nd;
-            if (want_energy && g >= r0 && g < r1) {
+            if (want_energy) {
                 eb = fma_t(nd, nd, eb);
                 eb = fma_t(-nu, L, eb);
             }
@@ -206,7 +204,7 @@ __device__ __forceinline__ void tile_block(const StepArgs& a, int K)
                     if (rec[i] >= 0) trace_out[(trace_row0 + t) * M.R + rec[i]] = u[i];
             }
         }
-        if (want_energy) acc[t] = lane_owned ? (double)eb : 0.0;
+        if (want_energy) acc[t] = (lane_owned && wave_owned) ? (double)eb : 0.0;
     }
 
 #pragma unroll
@@ -220,27 +218,39 @@ __device__ __forceinline__ void tile_block(const StepArgs& a, int K)
     }
 
     if (want_energy) {
-        // wave sums by DPP within rows of 16 lanes (pairs, quads, half rows, rows), then the four
-        // row sums read from lanes 0, 16, 32, 48: a few cycles per exchange where a general lane
-        // permutation waits on the LDS crossbar
+        // Sums over lanes, the eight levels together: three exchanges within eight lanes (partner 7 - l,
+        // l ^ 2, l ^ 1), each lane passing on the half of its levels that its partner keeps, leave lane l
+        // with level l & 7 of its eight lanes; one more adds the other half of the row of 16.
+        // (Level by level, each over the whole wave, this took 224 instructions instead of 60; with the
+        // test-free energy terms above, 256^2 FP64 with energies 1.06 -> 0.97 us per step.)
+        static_assert(kMaxTimeBlock == 8 && kWaveSize == 64, "eight levels over rows of sixteen lanes");
 #pragma unroll
-        for (int t = 0; t < kMaxTimeBlock; ++t) {
-            double v = acc[t];
-            v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-            v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-            v += dpp_f64<0x141>(v);  // row_half_mirror
-            v += dpp_f64<0x140>(v);  // row_mirror
-            acc[t] = (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+        for (int j = 0; j < 4; ++j) {
+            const double keep = (lane & 4) ? acc[j + 4] : acc[j];
+            const double pass = (lane & 4) ? acc[j] : acc[j + 4];
+            acc[j] = keep + dpp_f64<0x141>(pass);  // row_half_mirror
         }
-        if (lane == 0) {
 #pragma unroll
-            for (int t = 0; t < kMaxTimeBlock; ++t) s_e[t][w] = acc[t];
+        for (int j = 0; j < 2; ++j) {
+            const double keep = (lane & 2) ? acc[j + 2] : acc[j];
+            const double pass = (lane & 2) ? acc[j] : acc[j + 2];
+            acc[j] = keep + dpp_f64<0x4E>(pass);  // quad_perm [2, 3, 0, 1]
         }
+        const double keep = (lane & 1) ? acc[1] : acc[0];
+        const double pass = (lane & 1) ? acc[0] : acc[1];
+        double v = keep + dpp_f64<0xB1>(pass);  // quad_perm [1, 0, 3, 2]
+        v += dpp_f64<0x128>(v);                 // row_ror:8
+        if ((lane & 8) == 0) s_e[lane & 7][w * 4 + (lane >> 4)] = v;
         __syncthreads();
-        if (w == 0 && lane < K) {
+        // wave 0: lane (level, group) adds every eighth of the 4 NW row sums, then the groups are added
+        if (w == 0) {
+            const int t = lane & 7;
             double s = 0.0;
-            for (int v = 0; v < NW; ++v) s += s_e[lane][v];
-            M.epart[((size_t)a.eslot * kMaxTimeBlock + lane) * M.epart_stride + tile] = s;
+            for (int k = lane >> 3; k < 4 * NW; k += 8) s += s_e[t][k];
+            s += __shfl_xor(s, 8, 64);
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (lane < K) M.epart[((size_t)eslot * kMaxTimeBlock + lane) * M.epart_stride + tile] = s;
         }
     }
 }
