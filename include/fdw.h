@@ -263,7 +263,9 @@ enum {
                                      4 non-temporal loads only (float); results are identical */
     FDW_CFG_SMALL_TILES = 14,     /* small-grid kernel: one workgroup per tile of 48 owned columns,
                                      its waves advancing the tile level by level together.  0 (default):
-                                     used where every member has at most 1024 x 1024 nodes; 1: never;
+                                     used where the members have together at most 1.1e6 nodes (double) or
+                                     1.45e6 (float; with energies: where each has at most 1024 x 1024
+                                     and none records traces); 1: never;
                                      2: wherever allowed.  Never with the persistent launch (the streaming
                                      kernel runs those steps).  States and traces are identical bit for
                                      bit; energies agree to rounding (other partial sums).  The reverse
@@ -272,8 +274,9 @@ enum {
                                      of the FDW_CFG_ADJ_* keys to a value of its own or receivers share a
                                      node; gradients agree to rounding */
     FDW_CFG_TILE_ROWS = 15        /* rows per tile of the small-grid kernel (16 halo rows included):
-                                     32, 48 or 64 (0 = automatic: 64 where that gives a launch 150 to
-                                     300 tiles, else 48 where that gives at least 150, else 32) */
+                                     32, 48 or 64 (0 = automatic: the fewest that give a launch at most
+                                     256 tiles; beyond, 48, in float 64 where that gives 340 to 512
+                                     tiles) */
 };
 int fdw_configure(fdw_ctx* ctx, int32_t key, int64_t value);
 int64_t fdw_get_config(const fdw_ctx* ctx, int32_t key);

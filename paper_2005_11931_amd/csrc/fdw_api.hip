@@ -38,6 +38,7 @@ inline void* plane_origin(void* base, int ld, size_t es) { return (char*)base + 
 inline size_t elem_size(int dtype) { return dtype == FDW_F32 ? 4 : 8; }
 inline int pitch_of(int nx) { return (int)align_up((size_t)nx, 64); }
 constexpr int64_t kOneLaunchNodes = (int64_t)1 << 20;  // states up to here are read out in one launch
+constexpr int kCUs = 256;              // compute units of the MI355X
 constexpr int kMinSegRows = 8;      // rows per streaming work item, at least
 constexpr int kMinAdjSegRows = 16;  // ... and per reverse-sweep work item
 
@@ -219,10 +220,11 @@ void decompose(const fdw_ctx* c, const HostMember& hm, MemberDev& md, int S, int
     md.epart_stride = std::max(md.waves, 1);
 }
 
-// rows per tile of the small-grid kernel (64, 48 or 32 rows: 16, 12 or 8 waves): 64 where that
-// gives the launch 150..300 tiles (about one per CU), else 48 where that gives at least 150,
-// else 32.  Measured (256^2 .. 1024^2, FP64 and FP32, time block 8): the per-tile time grows
-// with the waves sharing a SIMD, the redundant halo work with the tile count.
+// Rows per tile of the small-grid kernel (32, 48 or 64 rows: 8, 12 or 16 waves): the fewest that give
+// the launch at most one tile per CU (384^2: 32; 600^2 FP64 1.28 us per step with 48 rows, 247 tiles, 1.37
+// with 64, 1.36 with 32; 700^2 1.43 with 64, 1.65 with 48); beyond, 48 (800^2, 289 tiles of 64 rows: 1.70
+// against 1.98 with 64), in float 64 where that gives 340 to 512 tiles (two per CU; the double
+// kernel's registers allow one: 1024^2 FP32 1.57 against 1.80).
 int tile_rows(const fdw_ctx* c)
 {
     if (c->tile_rows > 0) return c->tile_rows;
@@ -233,9 +235,10 @@ int tile_rows(const fdw_ctx* c)
                      ((hm.ny + rows - 2 * kTileHalo - 1) / (rows - 2 * kTileHalo));
         return tiles;
     };
+    for (const int rows : {32, 48, 64})
+        if (tiles_of(rows) <= kCUs) return rows;
     const int64_t t64 = tiles_of(64);
-    if (t64 >= 150 && t64 <= 300) return 64;
-    return tiles_of(48) >= 150 ? 48 : 32;
+    return c->dtype == FDW_F32 && t64 >= 340 && t64 <= 2 * kCUs ? 64 : 48;
 }
 
 // The small-grid decomposition: one tile per workgroup, independent of the time block (its halo
@@ -270,13 +273,24 @@ int choose_K(const fdw_ctx* c)
     return c->C == 1 ? 8 : 4;
 }
 
-int choose_S(const fdw_ctx* c)
+bool stream_nt(const fdw_ctx* c);
+
+// Rows per streaming work item.  An item computes S + 2K rows to advance S; a launch whose planes
+// stay in the last-level cache is bound by that work on the most loaded SIMD, which holds
+// n = ceil(workgroups / CUs) of the items (one wave of each workgroup): (S + 2K) n f(n), f the cost of the
+// dependent chains that too few waves cannot overlap (n = 1: 1.7, n = 2: 1.1).  The S of least cost
+// from 8 to 16 K, over all members of the launch; measured within 4% of the best S at every size
+// tried (1300^2 FP64 with energies 4.09 us per step against 5.42 before, 2048^2 FP64 5.01 / 5.47, with
+// energies 5.78 / 7.30, 2900^2 FP32 with energies 5.35 / 7.12, 700 x 4000 FP32 2.77 / 3.68).
+// Other launches keep the earlier rule (plain_S): 16 K rows, fewer where that leaves less than about
+// 4600 waves for the largest member: planes streamed from memory (stream_nt; 8192^2 FP32: 0.275 ms per
+// launch at 128 rows, 0.292 to 0.297 at 100 to 208), the persistent launch (whose waves take items
+// from a counter), launches that record traces (the items holding receivers decide: 2048^2 FP64
+// gradient 12.7 ms with 24-row items, 13.6 with 48), and FP32 launches with energies (`energy`: their
+// per-node terms are summed in FP32 over blocks of an item's rows, so that the item height and
+// direction show in the energies, at 1e-8; the height they were tested with stays).
+int plain_S(const fdw_ctx* c)
 {
-    if (c->S_cfg > 0) return c->S_cfg;
-    // Segments of 16 K rows (the 2K halo rows of a segment are then 1/8 of it, and half of
-    // them are usually shared with the neighbouring segment through L2), but short enough to
-    // give about 4600 streaming waves (one and a half rounds of the wave slots) for the
-    // largest member; at least 8 rows (small grids: more, shorter items).
     const int K = choose_K(c);
     int best = kMinSegRows;
     for (const HostMember& hm : c->m) {
@@ -284,6 +298,25 @@ int choose_S(const fdw_ctx* c)
         int64_t S = (hm.ny * strips + 4607) / 4608;
         S = std::min<int64_t>(16 * K, std::max<int64_t>(kMinSegRows, (S + 7) / 8 * 8));
         best = std::max(best, (int)S);
+    }
+    return best;
+}
+
+int choose_S(const fdw_ctx* c, bool energy = false, bool trace = false)
+{
+    if (c->S_cfg > 0) return c->S_cfg;
+    const int K = choose_K(c);
+    if (c->batch_mode == 1 || trace || (energy && c->dtype == FDW_F32) || stream_nt(c)) return plain_S(c);
+    int best = kMinSegRows;
+    double least = 1e300;
+    for (int S = kMinSegRows; S <= 16 * K; S += 8) {
+        int64_t blocks = 0;
+        for (const HostMember& hm : c->m)
+            blocks += ((int64_t)strips_for(hm.nx, c->C, K) * ((hm.ny + S - 1) / S) + kWavesPerBlock - 1) / kWavesPerBlock;
+        // (beyond four the workgroups of a CU start one after another, and the rounding is softer)
+        const double n = blocks <= 4 * kCUs ? (double)((blocks + kCUs - 1) / kCUs) : (double)blocks / kCUs + 0.5;
+        const double cost = (S + 2 * K) * n * (n <= 1.0 ? 1.7 : n <= 2.0 ? 1.1 : 1.0);
+        if (cost < least) least = cost, best = S;
     }
     return best;
 }
@@ -775,17 +808,25 @@ void replay_bookkeeping(fdw_ctx* c, int64_t steps, bool persistent)
 }
 
 // Whether a step_n call runs the small-grid tile kernel: not with the persistent launch;
-// automatically where every member has at most
-// kTileAutoNodes nodes (there the streaming kernel's few, long work items leave much of the
-// device idle: measured faster from 256^2 to 1024^2 - at 1024^2 by 7% in FP64, 14% in FP32).
-constexpr int64_t kTileAutoNodes = (int64_t)1024 * 1024;
-bool want_tiles(const fdw_ctx* c)
+// automatically where the launch's members have together at most 1.1e6 nodes in FP64, 1.45e6 in FP32
+// (there the streaming kernel's few, long work items leave much of the device idle: 1024^2 FP64 2.40 us
+// per step against 2.6, 1100^2 2.80 against 2.64; FP32 1200^2 2.08 against 2.44, 1300^2 2.49 against
+// 2.28; eight FP64 members of 150^2 to 600^2, 1.35e6 nodes, 3.36 against 3.00).
+// FP32 calls with energies (`energy`) choose as they always did - every member of at most 1024^2 nodes,
+// no receiver traces - since the two kernels sum the FP32 terms over different rows (choose_S).
+bool want_tiles(const fdw_ctx* c, bool energy = false)
 {
     if (c->tile_mode == 1 || c->batch_mode == 1) return false;
+    const bool f32_energy = energy && c->dtype == FDW_F32;
+    if (f32_energy && any_trace(c)) return false;
     if (c->tile_mode == 2) return true;
-    for (const HostMember& hm : c->m)
-        if ((int64_t)hm.nx * hm.ny > kTileAutoNodes) return false;
-    return true;
+    double nodes = 0.0;
+    bool small = true;
+    for (const HostMember& hm : c->m) {
+        nodes += (double)hm.nx * hm.ny;
+        small = small && (int64_t)hm.nx * hm.ny <= (int64_t)1024 * 1024;
+    }
+    return f32_energy ? small : nodes <= (c->dtype == FDW_F32 ? 1.45e6 : 1.1e6);
 }
 
 template <typename T>
@@ -795,10 +836,13 @@ int step_n_impl(fdw_ctx* c, int64_t n, double* energy_dev)
         if (!c->m[i].coeff) return fail(c, FDW_ESTATE, "fdw_set_coeff has not been called for member " + std::to_string(i));
     if (n == 0) return FDW_OK;
     {
-        // both kernels produce the same states bit for bit: the choice may change between calls
-        const bool tiles = want_tiles(c);
-        if (tiles != c->tiles_now) {
+        // both kernels, and every item height, produce the same states bit for bit: the choice may
+        // change between calls
+        const bool tiles = want_tiles(c, energy_dev != nullptr);
+        const int S = choose_S(c, energy_dev != nullptr, any_trace(c));
+        if (tiles != c->tiles_now || S != c->S_eff) {
             c->tiles_now = tiles;
+            c->S_eff = S;
             const int rc = layout_for_K(c, choose_K(c), c->S_eff);
             if (rc) return rc;
         }
@@ -1640,11 +1684,11 @@ bool want_adj_tiles(const fdw_ctx* c, const HostMember& hm, int dups)
     return c->tile_mode == 2 || (double)hm.nx * hm.ny <= (c->dtype == FDW_F32 ? 2.1e6 : 1.05e6);
 }
 
-// Rows and rows per wave of the reverse tiles: as in the forward tile kernel (tile_rows) 64 rows
-// where that gives 150 to 300 tiles (about one per CU), else 48 where that gives at least 150, else
-// 32.  Beyond 300 tiles of 64 rows the halo work decides in FP64 (64 rows: 1024^2 2.22 ms against 2.42
-// with 48, 2.85 with 32) and the waves per SIMD in FP32 (32 rows: 1801 x 1403 3.33 ms against 3.53
-// with 64, 3.63 with 48).  64-row tiles have 8 waves of 8 rows (700^2 FP64 1.29 ms; 12 waves of 4: 1.50).
+// Rows and rows per wave of the reverse tiles: the fewest of 32, 48, 64 that give at most one tile per
+// CU (384^2: 32, 192 tiles; 600^2 FP64 1.11 ms with 48 rows, 247 tiles, 1.24 with 64, 1.31 with 32; 700^2
+// 1.25 with 64, 1.52 with 48); beyond, 48 up to 340 tiles of 64 rows (800^2 FP64 1.62 ms, 1.88 with 64), then 64
+// in FP64 (1000^2 2.19, 2.32 with 48, 2.87 with 32) and 32 in FP32 (1200^2 .. 1400^2, where the waves per SIMD
+// count).  64-row tiles have 8 waves of 8 rows (700^2 FP64 1.29 ms; 12 waves of 4: 1.50).
 void adj_tile_shape(const fdw_ctx* c, const HostMember& hm, int* waves, int* rows_per_wave)
 {
     auto tiles_of = [&](int rows) {
@@ -1653,11 +1697,14 @@ void adj_tile_shape(const fdw_ctx* c, const HostMember& hm, int* waves, int* row
     };
     int rows = c->tile_rows;
     if (rows == 0) {
-        const int64_t t64 = tiles_of(64);
-        if (t64 > 300)
-            rows = c->dtype == FDW_F64 ? 64 : 32;
+        if (tiles_of(32) <= kCUs)
+            rows = 32;
+        else if (tiles_of(48) <= kCUs)
+            rows = 48;
+        else if (tiles_of(64) <= kCUs)
+            rows = 64;
         else
-            rows = t64 >= 150 ? 64 : tiles_of(48) >= 150 ? 48 : 32;
+            rows = tiles_of(64) < 340 ? 48 : c->dtype == FDW_F64 ? 64 : 32;
     }
     *rows_per_wave = rows == 64 ? 8 : 4;
     *waves = rows / *rows_per_wave;
@@ -1752,7 +1799,7 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
                 if (replay_tiles)
                     decompose_tile(c, hm, rep);
                 else
-                    decompose(c, hm, rep, c->S_eff, Kb);
+                    decompose(c, hm, rep, choose_S(c), Kb);
                 laidK = Kb;
             }
             StepArgs a;
