@@ -173,15 +173,16 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     }
     const int nblk = (r1 - r0 + 2 * K + U - 1) / U;
 
-    // FP32: two copies of the row loop.  Items that stay clear of the grid's first and last rows and
-    // whose rows hold no receiver (nearly all) run one without the tests for either: a test per
-    // level splits the row into pieces that the instruction scheduler cannot look across, and with
-    // one or two waves per SIMD nothing else fills the gaps of each level's dependent chain (1801 x 1403,
-    // 16-row items: 8.0 -> 7.4 us per reverse step).  FP64 waits for memory instead, and a second copy
-    // costs it registers (2048^2, K = 8: 14.7 us per step with one, 17.4 with two).
-    auto rows = [&](auto general) {
-    constexpr bool GENERAL = decltype(general)::value;
-    for (int blk = 0; blk < nblk; ++blk) {
+    // One block of U rows.  HEAD: the item's first block, as far as the item's own rows depend on it -
+    // what they need of level t starts at stream position 2t (2t - 1 for the y flux, and u is formed
+    // a row ahead) - which is a third of its levels' work, and no own row is finished in it.  A copy of
+    // the block without the other levels takes no registers from the row loop; skipping them by
+    // a branch in the loop took 20 to 45.  Gradients (reverse and traced forward): 2048^2 FP64
+    // 12.8 -> 11.8 ms; 1801 x 1403 FP32 5.67 -> 5.12.  (FP32 had two copies of the row loop, one without
+    // the tests for the grid's edge and for receivers: with the head on that copy alone, 5.37.)
+    auto rows = [&](auto head, int blk) __attribute__((always_inline)) {
+    constexpr bool HEAD = decltype(head)::value;
+    {
 #pragma unroll
         for (int s = 0; s < U; ++s) {
             const int p = blk * U + s;  // stream position of the row loaded last
@@ -228,12 +229,13 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
             }
 #pragma unroll
             for (int t = 1; t <= K; ++t) {
+                if (HEAD && 2 * t - 2 > s) break;
                 const int r = rfirst + dir * (p - t);  // grid row of stream position p - t
                 const int pr = pmod(s - t, 2);
                 const int pr1 = pmod(s - t + 1, 2);
                 const int q = pmod(s - t, K);
-                const bool rin = !GENERAL || ((r >= 1) && (r <= ny - 2));
-                const bool rown = (r >= r0) && (r < r1);
+                const bool rin = (r >= 1) && (r <= ny - 2);
+                const bool rown = !HEAD && (r >= r0) && (r < r1);
                 const int64_t n = a.n_top - t;  // time of this level's forward state
                 // u^{m-t}(r+1) = u^{m-t+1}(r+1) - du^{m-t+1}(r+1); u and du are zero on the
                 // Dirichlet rows at every level (and rows outside the grid load as zero), so
@@ -284,12 +286,12 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                 }
                 // Dirichlet rows keep du = mu = 0 (and with them u = lam = 0); the row test is
                 // wave-uniform, and the empty asm keeps it a scalar branch instead of selects
-                if (GENERAL && __builtin_expect(!rin, 0)) {
+                if (__builtin_expect(!rin, 0)) {
 #pragma unroll
                     for (int c = 0; c < C; ++c) nd[c] = nm[c] = T(0);
                     asm volatile("");
                 }
-                if (GENERAL && t == 1 && __builtin_expect(any_rec, 0)) {
+                if (t == 1 && __builtin_expect(any_rec, 0)) {
                     // receivers of row r in the columns this strip computes (halo included:
                     // every copy of a node takes its source), once per row
                     int kb = 0, ke = 0;
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                     RPb[q] = kb;
                     RPe[q] = ke;
                 }
-                if (GENERAL && __builtin_expect(any_rec && rin && RPb[q] < RPe[q], 0)) {
+                if (__builtin_expect(any_rec && rin && RPb[q] < RPe[q], 0)) {
                     const int kb = RPb[q], ke = RPe[q];
                     for (int k = kb; k < ke; ++k) {
                         const int off = rcol[k] - cb;
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
                 const int qd = pmod(s, K);
                 const int r = rfirst + dir * (p - K);
                 const double SL = lane_from_left(SX[qd][C - 1]);
-                if (r >= r0 && r < r1 && lane_owned) {
+                if (!HEAD && r >= r0 && r < r1 && lane_owned) {
                     const size_t off = (size_t)(ptrdiff_t)r * ld + (size_t)(ptrdiff_t)cb;
                     double o1[C], o2[C];
 #pragma unroll
@@ -382,10 +384,9 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     }
     };
     // (rows streamed past the item's halo, to fill the last unrolled block, influence nothing)
-    if (sizeof(T) == 8 || any_rec || r0 - K < 1 || r1 + K - 1 > ny - 2)
-        rows(BoolTag<true>{});
-    else
-        rows(BoolTag<false>{});
+    constexpr bool kHead = U <= K;
+    if constexpr (kHead) rows(BoolTag<true>{}, 0);
+    for (int blk = kHead ? 1 : 0; blk < nblk; ++blk) rows(BoolTag<false>{}, blk);
 }
 
 template <typename T, int K, int C>

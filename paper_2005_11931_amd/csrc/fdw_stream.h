@@ -454,8 +454,16 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
 #pragma unroll
     for (int q = 0; q < NB - 1; ++q) load_row(q, bu[q], bd[q], bh[q], bhy[q]);
 
-    {
-        for (int blk = 0; blk < nblk; ++blk) {
+    // One block of U rows.  HEAD: the item's first block, as far as the item's own rows depend on it:
+    // what they need of level t starts at stream position 2t (2t - 1 for the y flux), a quarter of the
+    // block's levels at K = 8, and none of them is owned.  That is 48 of the (S + 16) 8 level rows of an
+    // item, 15% at S = 24.  1531 x 1177 FP32 894 -> 819 us per solve, 2048^2 FP64 2076 -> 1903, eight FP32
+    // members with energies 2797 -> 2571, 8192^2 FP32 14820 -> 14540.  A copy of the block without the other
+    // levels takes few registers from the row loop (FP32 with energies 157 -> 161); skipping them by
+    // a branch in the loop took 16 to 40.
+    auto rows = [&](auto head_tag, int blk) __attribute__((always_inline)) {
+        constexpr bool HEAD = decltype(head_tag)::value;
+        {
             T eb[K];
 #pragma unroll
             for (int t = 0; t < K; ++t) eb[t] = T(0);
@@ -506,12 +514,13 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
                 // ---- levels 1..K
 #pragma unroll
                 for (int t = 1; t <= K; ++t) {
+                    if (HEAD && 2 * t - 1 > s) break;
                     const int r = rfirst + dir * (p - t);  // grid row of stream position p - t
                     const int pr = pmod(s - t, 2);         // parity index of row r
                     const int pr1 = pmod(s - t + 1, 2);    // ... of the next row in the stream, r + dir
                     const int q = pmod(s - t, K);          // coefficient ring index of row r
                     const bool rin = (r >= 1) && (r <= ny - 2);
-                    const bool rown = (r >= r0) && (r < r1);
+                    const bool rown = !HEAD && (r >= r0) && (r < r1);
                     const T right = lane_from_right(Ur[t - 1][pr][0]);
                     T F[C];
 #pragma unroll
@@ -560,7 +569,7 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
                         // at K >= 3)
                         asm volatile("" : "+v"(eb[t - 1]));
                     }
-                    if (want_trace && __builtin_expect(item_rec, 0)) {
+                    if (want_trace && !HEAD && __builtin_expect(item_rec, 0)) {
                         // receivers of row r in this strip's owned columns, looked up once when
                         // the row enters level 1 (none for rows the item does not own or that lie
                         // on the boundary), and entered in the row's slots
@@ -630,12 +639,17 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
                 // keep the scheduler from interleaving consecutive rows (bounds register pressure)
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (want_energy && lane_owned) {
+            if (want_energy && !HEAD && lane_owned) {
 #pragma unroll
                 for (int t = 0; t < K; ++t) acc[t] += (double)eb[t];
             }
         }
-    }
+    };
+    // (not in FP32 with faces and energies, where it costs the third wave per SIMD: 166 -> 177 registers;
+    // with U > K the first block already holds own rows)
+    constexpr bool kHead = U <= K && !(sizeof(T) == 4 && FACE && want_energy);
+    if constexpr (kHead) rows(BoolTag<true>{}, 0);
+    for (int blk = kHead ? 1 : 0; blk < nblk; ++blk) rows(BoolTag<false>{}, blk);
 
     if (want_energy) {
 #pragma unroll
