@@ -523,11 +523,19 @@ __device__ __forceinline__ int find_member(const MemberDev* table, int first, in
     return m;
 }
 
-// The double trace-recording variant (one column per lane, nodal coefficients) is held to four
-// waves per SIMD (128 registers, a few values spilled): its 135 registers otherwise leave three,
-// and the traced forward run of a gradient evaluation measured 5% faster with four.
+// Waves per SIMD a variant is held to.  The double trace-recording variant (one column per lane, nodal
+// coefficients): four (128 registers, seven values spilled); its 135 registers otherwise leave three,
+// and the traced forward run of a gradient evaluation measured 5% faster with four.  The same with
+// energies, time block 8: three (168 registers without a spill; left alone it takes 181 and leaves two:
+// 1500^2 with 64 receivers, 80 steps, 582 us, now 486; 2500^2 1108, now 1002).
 template <typename T, int K, int C, int FACE, int MODE>
-__global__ __launch_bounds__(kWaveSize * kWavesPerBlock, (sizeof(T) == 8 && C == 1 && FACE == 0 && MODE == 2) ? 4 : 1) void k_step(StepArgs a)
+constexpr int min_waves()
+{
+    if (sizeof(T) == 8 && C == 1 && FACE == 0) return MODE == 2 ? 4 : (MODE == 3 && K == 8) ? 3 : 1;
+    return 1;
+}
+template <typename T, int K, int C, int FACE, int MODE>
+__global__ __launch_bounds__(kWaveSize * kWavesPerBlock, (min_waves<T, K, C, FACE, MODE>())) void k_step(StepArgs a)
 {
     int lb = xcd_remap(blockIdx.x, a.total_blocks);
     if (a.reverse) lb = a.total_blocks - 1 - lb;

@@ -17,6 +17,7 @@ VARIANTS = [
     ("float, 8, 2, 1, 5", 168),
     ("float, 6, 4, 1, 1", 256),  # the same with 4 columns per lane at its deepest time block
     ("float, 6, 4, 1, 5", 256),
+    ("double, 8, 1, 0, 3", 168),  # FP64 with traces and energies
 ]
 
 
