@@ -263,9 +263,10 @@ enum {
                                      4 non-temporal loads only (float); results are identical */
     FDW_CFG_SMALL_TILES = 14,     /* small-grid kernel: one workgroup per tile of 48 owned columns,
                                      its waves advancing the tile level by level together.  0 (default):
-                                     used where the members have together at most 1.1e6 nodes (double) or
-                                     1.45e6 (float; with energies: where each has at most 1024 x 1024
-                                     and none records traces); 1: never;
+                                     used where the members of one launch (all of them, or a single one in
+                                     a family whose members differ in coefficient layout) have together at
+                                     most 1.1e6 nodes (double) or 1.45e6 (float; with energies: where each
+                                     has at most 1024 x 1024 and none records traces); 1: never;
                                      2: wherever allowed.  Never with the persistent launch (the streaming
                                      kernel runs those steps).  States and traces are identical bit for
                                      bit; energies agree to rounding (other partial sums).  The reverse

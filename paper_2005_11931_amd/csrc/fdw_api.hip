@@ -220,20 +220,39 @@ void decompose(const fdw_ctx* c, const HostMember& hm, MemberDev& md, int S, int
     md.epart_stride = std::max(md.waves, 1);
 }
 
+// The launches of one time block: all members together where they share a coefficient layout, else one
+// by one (launch_block); `only` >= 0 stands for the launches of that member alone (the replay of
+// fdw_adjoint).  f(first member, members).  The rules below go by what one launch holds (64 steps of
+// eight members of 512^2 whose layouts alternate: FP64 684 us, 1180 with rules over the whole family, FP32
+// 513 and 1309; replay and reverse sweep, 200 steps, of one of eight FP64 members of 512^2: 716 and 892).
+template <typename F>
+void for_launches(const fdw_ctx* c, int only, F f)
+{
+    if (only >= 0) return f(only, 1);
+    bool one_layout = true;
+    for (const HostMember& hm : c->m) one_layout = one_layout && hm.face == c->m[0].face;
+    if (one_layout) return f(0, c->count);
+    for (int i = 0; i < c->count; ++i) f(i, 1);
+}
+
 // Rows per tile of the small-grid kernel (32, 48 or 64 rows: 8, 12 or 16 waves): the fewest that give
-// the launch at most one tile per CU (384^2: 32; 600^2 FP64 1.28 us per step with 48 rows, 247 tiles, 1.37
+// a launch at most one tile per CU (384^2: 32; 600^2 FP64 1.28 us per step with 48 rows, 247 tiles, 1.37
 // with 64, 1.36 with 32; 700^2 1.43 with 64, 1.65 with 48); beyond, 48 (800^2, 289 tiles of 64 rows: 1.70
 // against 1.98 with 64), in float 64 where that gives 340 to 512 tiles (two per CU; the double
 // kernel's registers allow one: 1024^2 FP32 1.57 against 1.80).
-int tile_rows(const fdw_ctx* c)
+int tile_rows(const fdw_ctx* c, int only = -1)
 {
     if (c->tile_rows > 0) return c->tile_rows;
     auto tiles_of = [&](int rows) {
-        int64_t tiles = 0;
-        for (const HostMember& hm : c->m)
-            tiles += (int64_t)((hm.nx + kTileCols - 1) / kTileCols) *
-                     ((hm.ny + rows - 2 * kTileHalo - 1) / (rows - 2 * kTileHalo));
-        return tiles;
+        int64_t most = 0;
+        for_launches(c, only, [&](int first, int n) {
+            int64_t tiles = 0;
+            for (int i = first; i < first + n; ++i)
+                tiles += (int64_t)((c->m[i].nx + kTileCols - 1) / kTileCols) *
+                         ((c->m[i].ny + rows - 2 * kTileHalo - 1) / (rows - 2 * kTileHalo));
+            most = std::max(most, tiles);
+        });
+        return most;
     };
     for (const int rows : {32, 48, 64})
         if (tiles_of(rows) <= kCUs) return rows;
@@ -243,9 +262,8 @@ int tile_rows(const fdw_ctx* c)
 
 // The small-grid decomposition: one tile per workgroup, independent of the time block (its halo
 // covers the deepest one).  waves = blocks = tiles (one energy partial per tile and level).
-void decompose_tile(const fdw_ctx* c, const HostMember& hm, MemberDev& md)
+void decompose_tile(const HostMember& hm, MemberDev& md, int rows)
 {
-    const int rows = tile_rows(c);
     md.seg_rows = rows - 2 * kTileHalo;
     md.segs = (hm.ny + md.seg_rows - 1) / md.seg_rows;
     md.strips = (hm.nx + kTileCols - 1) / kTileCols;
@@ -279,8 +297,8 @@ bool stream_nt(const fdw_ctx* c);
 // stay in the last-level cache is bound by that work on the most loaded SIMD, which holds
 // n = ceil(workgroups / CUs) of the items (one wave of each workgroup): (S + 2K) n f(n), f the cost of the
 // dependent chains that too few waves cannot overlap (n = 1: 1.7, n = 2: 1.1).  The S of least cost
-// from 8 to 16 K, over all members of the launch; measured within 4% of the best S at every size
-// tried (1300^2 FP64 with energies 4.09 us per step against 5.42 before, 2048^2 FP64 5.01 / 5.47, with
+// from 8 to 16 K, over all members of a launch, summed over the launches; measured within 4% of the
+// best S at every size tried (1300^2 FP64 with energies 4.09 us per step against 5.42 before, 2048^2 FP64 5.01 / 5.47, with
 // energies 5.78 / 7.30, 2900^2 FP32 with energies 5.35 / 7.12, 700 x 4000 FP32 2.77 / 3.68).
 // Other launches keep the earlier rule (plain_S): 16 K rows, fewer where that leaves less than about
 // 4600 waves for the largest member: planes streamed from memory (stream_nt; 8192^2 FP32: 0.275 ms per
@@ -289,11 +307,13 @@ bool stream_nt(const fdw_ctx* c);
 // gradient 12.7 ms with 24-row items, 13.6 with 48), and FP32 launches with energies (`energy`: their
 // per-node terms are summed in FP32 over blocks of an item's rows, so that the item height and
 // direction show in the energies, at 1e-8; the height they were tested with stays).
-int plain_S(const fdw_ctx* c)
+int plain_S(const fdw_ctx* c, int only)
 {
     const int K = choose_K(c);
     int best = kMinSegRows;
-    for (const HostMember& hm : c->m) {
+    for (int i = 0; i < c->count; ++i) {
+        if (only >= 0 && i != only) continue;
+        const HostMember& hm = c->m[i];
         const int64_t strips = strips_for(hm.nx, c->C, K);
         int64_t S = (hm.ny * strips + 4607) / 4608;
         S = std::min<int64_t>(16 * K, std::max<int64_t>(kMinSegRows, (S + 7) / 8 * 8));
@@ -302,20 +322,24 @@ int plain_S(const fdw_ctx* c)
     return best;
 }
 
-int choose_S(const fdw_ctx* c, bool energy = false, bool trace = false)
+int choose_S(const fdw_ctx* c, bool energy = false, bool trace = false, int only = -1)
 {
     if (c->S_cfg > 0) return c->S_cfg;
     const int K = choose_K(c);
-    if (c->batch_mode == 1 || trace || (energy && c->dtype == FDW_F32) || stream_nt(c)) return plain_S(c);
+    if (c->batch_mode == 1 || trace || (energy && c->dtype == FDW_F32) || stream_nt(c)) return plain_S(c, only);
     int best = kMinSegRows;
     double least = 1e300;
     for (int S = kMinSegRows; S <= 16 * K; S += 8) {
-        int64_t blocks = 0;
-        for (const HostMember& hm : c->m)
-            blocks += ((int64_t)strips_for(hm.nx, c->C, K) * ((hm.ny + S - 1) / S) + kWavesPerBlock - 1) / kWavesPerBlock;
-        // (beyond four the workgroups of a CU start one after another, and the rounding is softer)
-        const double n = blocks <= 4 * kCUs ? (double)((blocks + kCUs - 1) / kCUs) : (double)blocks / kCUs + 0.5;
-        const double cost = (S + 2 * K) * n * (n <= 1.0 ? 1.7 : n <= 2.0 ? 1.1 : 1.0);
+        double cost = 0.0;
+        for_launches(c, only, [&](int first, int nm) {
+            int64_t blocks = 0;
+            for (int i = first; i < first + nm; ++i)
+                blocks += ((int64_t)strips_for(c->m[i].nx, c->C, K) * ((c->m[i].ny + S - 1) / S) + kWavesPerBlock - 1) /
+                          kWavesPerBlock;
+            // (beyond four the workgroups of a CU start one after another, and the rounding is softer)
+            const double n = blocks <= 4 * kCUs ? (double)((blocks + kCUs - 1) / kCUs) : (double)blocks / kCUs + 0.5;
+            cost += (S + 2 * K) * n * (n <= 1.0 ? 1.7 : n <= 2.0 ? 1.1 : 1.0);
+        });
         if (cost < least) least = cost, best = S;
     }
     return best;
@@ -359,10 +383,11 @@ int push_member(fdw_ctx* c, int m, hipStream_t s = nullptr)
 int layout_for_K(fdw_ctx* c, int K, int S, hipStream_t st = nullptr)
 {
     int base = 0;
+    const int rows = tile_rows(c);
     for (int i = 0; i < c->count; ++i) {
         MemberDev& md = c->tab[i];
         if (c->tiles_now)
-            decompose_tile(c, c->m[i], md);
+            decompose_tile(c->m[i], md, rows);
         else
             decompose(c, c->m[i], md, S, K);
         md.block_base = base;
@@ -808,25 +833,29 @@ void replay_bookkeeping(fdw_ctx* c, int64_t steps, bool persistent)
 }
 
 // Whether a step_n call runs the small-grid tile kernel: not with the persistent launch;
-// automatically where the launch's members have together at most 1.1e6 nodes in FP64, 1.45e6 in FP32
+// automatically where the members of every launch have together at most 1.1e6 nodes in FP64, 1.45e6 in FP32
 // (there the streaming kernel's few, long work items leave much of the device idle: 1024^2 FP64 2.40 us
 // per step against 2.6, 1100^2 2.80 against 2.64; FP32 1200^2 2.08 against 2.44, 1300^2 2.49 against
 // 2.28; eight FP64 members of 150^2 to 600^2, 1.35e6 nodes, 3.36 against 3.00).
 // FP32 calls with energies (`energy`) choose as they always did - every member of at most 1024^2 nodes,
 // no receiver traces - since the two kernels sum the FP32 terms over different rows (choose_S).
-bool want_tiles(const fdw_ctx* c, bool energy = false)
+bool want_tiles(const fdw_ctx* c, bool energy = false, int only = -1)
 {
     if (c->tile_mode == 1 || c->batch_mode == 1) return false;
     const bool f32_energy = energy && c->dtype == FDW_F32;
     if (f32_energy && any_trace(c)) return false;
     if (c->tile_mode == 2) return true;
-    double nodes = 0.0;
+    double most = 0.0;
     bool small = true;
-    for (const HostMember& hm : c->m) {
-        nodes += (double)hm.nx * hm.ny;
-        small = small && (int64_t)hm.nx * hm.ny <= (int64_t)1024 * 1024;
-    }
-    return f32_energy ? small : nodes <= (c->dtype == FDW_F32 ? 1.45e6 : 1.1e6);
+    for_launches(c, only, [&](int first, int n) {
+        double nodes = 0.0;
+        for (int i = first; i < first + n; ++i) {
+            nodes += (double)c->m[i].nx * c->m[i].ny;
+            small = small && (int64_t)c->m[i].nx * c->m[i].ny <= (int64_t)1024 * 1024;
+        }
+        most = std::max(most, nodes);
+    });
+    return f32_energy ? small : most <= (c->dtype == FDW_F32 ? 1.45e6 : 1.1e6);
 }
 
 template <typename T>
@@ -1782,7 +1811,9 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
         HIPCHK(c, launch_start<T>(&rep, hm.u0, hm.u1, (T)hm.tau, 0, nullptr, c->red, s));
         int64_t n = 1;
         const int Kf = choose_K(c);
-        const bool replay_tiles = want_tiles(c);  // (both kernels give the same states bit for bit)
+        // (both kernels, and every item height, give the same states bit for bit)
+        const bool replay_tiles = want_tiles(c, false, m);
+        const int replay_rows = tile_rows(c, m);
         int laidK = -1;
         auto store_ckpt = [&](int64_t step) -> int {
             const int64_t k = step / ck - 1;
@@ -1797,9 +1828,9 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
             const int Kb = (int)std::min<int64_t>(Kf, next - n);
             if (Kb != laidK) {
                 if (replay_tiles)
-                    decompose_tile(c, hm, rep);
+                    decompose_tile(hm, rep, replay_rows);
                 else
-                    decompose(c, hm, rep, choose_S(c), Kb);
+                    decompose(c, hm, rep, choose_S(c, false, false, m), Kb);
                 laidK = Kb;
             }
             StepArgs a;
@@ -1817,7 +1848,7 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
             a.stream_nt = rep.stream_nt;
             a.reverse = 0;
             if (replay_tiles)
-                HIPCHK(c, launch_step_tile<T>(a, Kb, hm.face, tile_rows(c) / kTileRowsPerWave, rep.blocks, s));
+                HIPCHK(c, launch_step_tile<T>(a, Kb, hm.face, replay_rows / kTileRowsPerWave, rep.blocks, s));
             else
                 HIPCHK(c, launch_step<T>(a, Kb, c->C, hm.face, rep.blocks, s));
             cur ^= 1;
