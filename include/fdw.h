@@ -237,8 +237,8 @@ enum {
                                  (double); 0 = default */
     FDW_CFG_ADJ_TIME_BLOCK = 7,  /* reverse steps per launch of the adjoint sweep: 1..6 with 1 (double) or
                                     2 (float) columns per lane, else 1..4 (0 = automatic: 6 with those
-                                    lane layouts, the defaults, else 4; double with 1 column then takes 8
-                                    steps per launch, reported as 6) */
+                                    lane layouts, the defaults, else 4).  6 stands for the deepest block
+                                    there is: double with 1 column runs 8 steps per launch */
     FDW_CFG_ADJ_LANE_COLUMNS = 8, /* columns per lane of the adjoint sweep: 2 or 4 (float), 1 or 2 (double);
                                      0 = default (2 for float, 1 for double) */
     FDW_CFG_ADJ_SEGMENT_ROWS = 9, /* rows per work item of the adjoint sweep, 16..4096 (0 = automatic: the
@@ -272,8 +272,8 @@ enum {
                                      bit; energies agree to rounding (other partial sums).  The reverse
                                      sweep of fdw_adjoint has such a kernel too (up to 8 reverse steps per
                                      launch): it runs where this key allows it, unless the caller set one
-                                     of the FDW_CFG_ADJ_* keys to a value of its own or receivers share a
-                                     node; gradients agree to rounding */
+                                     of the FDW_CFG_ADJ_* keys to another value than its default or
+                                     receivers share a node; gradients agree to rounding */
     FDW_CFG_TILE_ROWS = 15        /* rows per tile of the small-grid kernel (16 halo rows included):
                                      32, 48 or 64 (0 = automatic: the fewest that give a launch at most
                                      256 tiles; beyond, 48, in float 64 where that gives 340 to 512
@@ -304,9 +304,10 @@ int fdw_autotune(fdw_ctx* ctx, int32_t steps, int64_t* best_out);
  * arguments (as for fdw_adjoint; the gradient goes to grad_scratch, device double [ny][nx], and
  * the forward state is left unchanged) for each candidate (reverse time block, columns per lane,
  * rows per work item) and applies the fastest.  With checkpoints recorded by the forward run in
- * adj_ws the candidates time the reverse sweep alone.  The search times the streaming sweep only (as
- * fdw_autotune; where the small-grid tiles run they keep running).  Cached like fdw_autotune.  best_out (host,
- * may be NULL) receives {adj_time_block, adj_segment_rows (0 = automatic), adj_lane_columns}. */
+ * adj_ws the candidates time the reverse sweep alone.  Where the reverse tiles of small grids run
+ * (FDW_CFG_SMALL_TILES) there is nothing to choose: the defaults are applied, and the tiles keep running.
+ * Cached like fdw_autotune.  best_out (host, may be NULL) receives {adj_time_block, adj_segment_rows
+ * (0 = automatic), adj_lane_columns}; setting these three on another context has the same effect. */
 int fdw_autotune_adjoint(fdw_ctx* ctx, int32_t member, const int32_t* recv_ij, int32_t R, const double* trace_grad,
                          int32_t ckpt_every, void* adj_ws, size_t adj_ws_bytes, double* grad_scratch,
                          int64_t* best_out);

@@ -101,7 +101,9 @@ struct fdw_ctx {
     int C = 4;  // columns per lane of the streaming kernels
     int adjK = 2, adjC = 2;  // time block and columns per lane of the reverse sweep
     int adjS_cfg = 0;        // rows per reverse work item (0 = automatic)
-    unsigned adj_set = 0;    // bits: reverse time block, lane columns, item rows set by the caller
+    // bits: reverse time block, lane columns, item rows that the caller set to another value than the default
+    unsigned adj_set = 0;
+    bool adj_tiles_ran = false;  // the last fdw_adjoint ran the reverse tile kernel
     // checkpoints of the adjoint stored by the forward run of one member (member < 0: off)
     struct {
         int member = -1;
@@ -282,6 +284,16 @@ int energy_group_cap(const fdw_ctx* c, int i)
 
 // reverse-sweep configurations with one 8-byte value per lane and row (time blocks up to 6)
 bool adj_narrow(int dtype, int C) { return (dtype == FDW_F64) ? C == 1 : C == 2; }
+constexpr int kAdjDefaultK = 6;
+int adj_default_C(int dtype) { return dtype == FDW_F64 ? 1 : 2; }
+
+// The caller sets one of the three reverse-sweep values, `old` so far.  Only a value that differs from the
+// default counts as the caller's own (it selects the streaming sweep, want_adj_tiles): setting again
+// what fdw_get_config or the tuner reported changes nothing.
+void mark_adj(fdw_ctx* c, unsigned bit, int64_t old, int64_t v, int64_t dflt)
+{
+    if (v != old) c->adj_set = (c->adj_set & ~bit) | (v != dflt ? bit : 0u);
+}
 
 int choose_K(const fdw_ctx* c)
 {
@@ -1098,8 +1110,8 @@ int fdw_init(const fdw_problem* problems, int32_t count, void* workspace, size_t
     c->count = count;
     c->dtype = problems[0].dtype;
     c->C = default_cols_per_lane(c->dtype);
-    c->adjC = (c->dtype == FDW_F64) ? 1 : 2;
-    c->adjK = 6;  // the deepest reverse blocks at two waves per SIMD (the default lane layouts allow it)
+    c->adjC = adj_default_C(c->dtype);
+    c->adjK = kAdjDefaultK;  // the deepest reverse blocks at two waves per SIMD (the default lane layouts allow it)
     c->stream = (hipStream_t)hip_stream;
     if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) {
         delete c;
@@ -1506,7 +1518,6 @@ int fdw_configure(fdw_ctx* c, int32_t key, int64_t v)
         }
         return FDW_OK;
     }
-    const bool set = v != 0;  // (a value of the caller's own, not the default)
     switch (key) {
     case FDW_CFG_TIME_BLOCK:
         if (v < 0 || v > kMaxTimeBlock || (c->dtype == FDW_F64 && c->C == 2 && v > 4) || (c->C == 4 && v > 6))
@@ -1545,8 +1556,8 @@ int fdw_configure(fdw_ctx* c, int32_t key, int64_t v)
         if (v < 1 || v > 6 || (v > 4 && !adj_narrow(c->dtype, c->adjC)))
             return fail(c, FDW_EINVAL, "adjoint time block must be 1..6 (double with 1 column per lane, float with 2) "
                                        "or 1..4");
+        mark_adj(c, 1u, c->adjK, v, kAdjDefaultK);
         c->adjK = (int)v;
-        c->adj_set = (c->adj_set & ~1u) | (set ? 1u : 0u);
         break;
     case FDW_CFG_ADJ_LANE_COLUMNS:
         if (v == 0) v = (c->dtype == FDW_F64) ? 1 : 2;
@@ -1554,13 +1565,13 @@ int fdw_configure(fdw_ctx* c, int32_t key, int64_t v)
             return fail(c, FDW_EINVAL, "adjoint lane columns must be 2 or 4 (float) / 1 or 2 (double)");
         if (c->adjK > 4 && !adj_narrow(c->dtype, (int)v))
             return fail(c, FDW_EINVAL, "adjoint time blocks above 4 need 1 (double) or 2 (float) columns per lane");
+        mark_adj(c, 2u, c->adjC, v, adj_default_C(c->dtype));
         c->adjC = (int)v;
-        c->adj_set = (c->adj_set & ~2u) | (set ? 2u : 0u);
         break;
     case FDW_CFG_ADJ_SEGMENT_ROWS:
         if (v != 0 && (v < kMinAdjSegRows || v > 4096)) return fail(c, FDW_EINVAL, "adjoint segment rows must be 0 or 16..4096");
+        mark_adj(c, 4u, c->adjS_cfg, v, 0);
         c->adjS_cfg = (int)v;
-        c->adj_set = (c->adj_set & ~4u) | (set ? 4u : 0u);
         break;
     case FDW_CFG_CHECK_ENERGY:
         if (v != 0 && v != 1) return fail(c, FDW_EINVAL, "check_energy must be 0 or 1");
@@ -1656,14 +1667,14 @@ int64_t fdw_get_config(const fdw_ctx* c, int32_t key)
 // =============================================================================================
 namespace {
 
-// Reverse steps per launch.  The automatic choice in double with one column per lane is 8 (reported
-// as 6, the largest block the caller can set): the sweep waits for memory there, and 8 levels move
-// 11 words per node 6 levels moved (2048^2: 16.9 -> 13.3 us per step, 4096^2: 63 -> 49).  In float 8 levels
-// need more than the 256 registers of two waves per SIMD (3000^2: 20.4 us per step with 6, 19 to 24 with 8).
+// Reverse steps per launch.  The deepest block the caller can set, 6 and the default, stands for 8 in
+// double with one column per lane, whoever set it: the sweep waits for memory there, and 8 levels move
+// the 11 words per node that 6 levels moved (2048^2: 16.9 -> 13.3 us per step, 4096^2: 63 -> 49).  In
+// float 8 levels need more than the 256 registers of two waves per SIMD (3000^2: 20.4 us per step with
+// 6, 19 to 24 with 8).
 int adjoint_K(const fdw_ctx* c)
 {
-    const bool automatic = c->adjK == 6 && !(c->adj_set & 1u);
-    return automatic && c->dtype == FDW_F64 && c->adjC == 1 ? 8 : c->adjK;
+    return c->adjK == kAdjDefaultK && c->dtype == FDW_F64 && c->adjC == 1 ? 8 : c->adjK;
 }
 
 void adj_decompose(const fdw_ctx* c, const HostMember& hm, int K, int S, AdjArgs& a)
@@ -1705,7 +1716,7 @@ int choose_adj_S(const fdw_ctx* c, const HostMember& hm, int K, bool split)
 // nodes in FP64 and 2.1e6 in FP32 (gradient with 256 steps: 384^2 FP64 0.85 ms against 2.38 with the
 // streaming sweep, 1024^2 2.22 against 2.31, 1100^2 3.11 against 2.69; FP32 1024^2 1.73 against 2.62,
 // 1400^2 2.81 against 2.91, 1500^2 3.00 against 2.98, 1801 x 1403 3.29 against 2.98); not where the caller set the streaming sweep's own
-// parameters, and not with coincident receivers (`dups`: the tile kernel takes one source per
+// parameters (to other values than the defaults), and not with coincident receivers (`dups`: the tile kernel takes one source per
 // node).
 bool want_adj_tiles(const fdw_ctx* c, const HostMember& hm, int dups)
 {
@@ -1892,6 +1903,7 @@ int adjoint_impl(fdw_ctx* c, int m, const int32_t* recv_ij, int R, const double*
     int fcur = recorded ? 1 : cur;  // the first reverse output goes to the other state plane
     int lcur = 0;
     const bool tiles = want_adj_tiles(c, hm, st[1]);
+    c->adj_tiles_ran = tiles;
     int tile_waves = 0, tile_rw = 0;
     adj_tile_shape(c, hm, &tile_waves, &tile_rw);
     const int Kr = tiles ? kTileHalo : adjoint_K(c);
@@ -2201,7 +2213,7 @@ extern "C" int fdw_autotune_adjoint(fdw_ctx* c, int32_t m, const int32_t* recv_i
     const HostMember& hm = c->m[m];
     std::ostringstream key;
     key << tune_key(c) << " adj m" << m << " c" << ckpt_every << " R" << R;
-    int bestK = c->adjK, bestC = c->adjC, bestS = c->adjS_cfg;
+    int bestK = kAdjDefaultK, bestC = adj_default_C(c->dtype), bestS = 0;
     int cK = 0, cS = 0, cC = 0;
     int cP = 0;
     if (cache_lookup(key.str(), &cK, &cS, &cC, &cP)) {
@@ -2209,23 +2221,24 @@ extern "C" int fdw_autotune_adjoint(fdw_ctx* c, int32_t m, const int32_t* recv_i
         bestS = cS;
         bestC = cC;
     } else {
-        // (columns per lane, reverse time block) pairs the kernels support, x rows per item (0: automatic)
+        // (columns per lane, reverse time block) pairs the kernels support, x rows per item (0: automatic),
+        // the defaults first: where these run the reverse tiles, which have no such parameters, they are the
+        // choice
         std::vector<std::pair<int, int>> CK;
-        if (c->dtype == FDW_F64) {
-            for (int K = 2; K <= 6; ++K) CK.push_back({1, K});
-            for (int K = 2; K <= 4; ++K) CK.push_back({2, K});
-        } else {
-            for (int K = 2; K <= 6; ++K) CK.push_back({2, K});
-            for (int K = 2; K <= 4; ++K) CK.push_back({4, K});
-        }
+        for (int K = kAdjDefaultK; K >= 2; --K) CK.push_back({bestC, K});
+        for (int K = 2; K <= 4; ++K) CK.push_back({2 * bestC, K});
         const int Ss[] = {0, 16, 32, 64};
         const int saveK = c->adjK, saveC = c->adjC, saveS = c->adjS_cfg;
+        const unsigned saveSet = c->adj_set;
         hipEvent_t e0, e1;
         HIPCHK(c, hipEventCreate(&e0));
         HIPCHK(c, hipEventCreate(&e1));
         float best = 1e30f;
+        c->adj_set = 0;
+        c->adj_tiles_ran = false;
         for (const auto& ck : CK) {
             for (int S : Ss) {
+                if (c->adj_tiles_ran) break;
                 if (S > 0 && (S < 4 * ck.second || S > hm.ny)) continue;
                 c->adjC = ck.first;
                 c->adjK = ck.second;
@@ -2233,16 +2246,13 @@ extern "C" int fdw_autotune_adjoint(fdw_ctx* c, int32_t m, const int32_t* recv_i
                 std::vector<float> ts;
                 for (int rep = 0; rep < 2; ++rep) {
                     HIPCHK(c, hipEventRecord(e0, c->stream));
-                    // (the streaming sweep: the small-grid tiles have no such parameters)
-                    const int saveTiles = c->tile_mode;
-                    c->tile_mode = 1;
                     rc = fdw_adjoint(c, m, recv_ij, R, trace_grad, ckpt_every, adj_ws, adj_ws_bytes, grad_scratch,
                                      nullptr);
-                    c->tile_mode = saveTiles;
                     if (rc) {
                         c->adjK = saveK;
                         c->adjC = saveC;
                         c->adjS_cfg = saveS;
+                        c->adj_set = saveSet;
                         hipEventDestroy(e0);
                         hipEventDestroy(e1);
                         return rc;
@@ -2266,6 +2276,7 @@ extern "C" int fdw_autotune_adjoint(fdw_ctx* c, int32_t m, const int32_t* recv_i
         hipEventDestroy(e1);
         cache_store(key.str(), bestK, bestS, bestC, 0);
     }
+    c->adj_set = 0;
     c->adjK = bestK;
     c->adjC = bestC;
     c->adjS_cfg = bestS;

@@ -1,0 +1,103 @@
+"""Settings of the reverse sweep.  Setting a value that fdw_get_config or the tuner reported changes
+nothing: the same kernels run, so that the gradients are the same bit for bit (other time blocks and the
+reverse tiles sum them in another order).  A tuned configuration is the one that runs afterwards."""
+import numpy as np
+import pytest
+
+from paper_2005_11931_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# (type, nodes a side): reverse tiles at 384 (at most 1.05e6 nodes in FP64, 2.1e6 in FP32), the streaming
+# sweep at 1100 and 1500
+SIZES = [("f64", 384), ("f32", 384), ("f64", 1100), ("f32", 1500)]
+
+
+def _problem(n, nsteps=40, nrecv=16):
+    import torch
+
+    case, _ = I.adjoint_case(n=n, nsteps=nsteps, nrecv=nrecv)
+    return case, torch.as_tensor(case.receivers), torch.as_tensor(np.random.default_rng(9).normal(size=(nsteps + 1, nrecv)))
+
+
+def _keys(fdw):
+    return (fdw.FDW_CFG_ADJ_TIME_BLOCK, fdw.FDW_CFG_ADJ_SEGMENT_ROWS, fdw.FDW_CFG_ADJ_LANE_COLUMNS)
+
+
+def _gradient(case, dt, rec, tg, settings=()):
+    from paper_2005_11931_amd import fdw
+
+    s = fdw.solver_for_case(case, dtype=dt)
+    for k, v in settings:
+        s.configure(k, v)
+    g = s.adjoint(rec, tg, ckpt_every=20).cpu().numpy()
+    s.close()
+    return g
+
+
+@pytest.mark.parametrize("dtype_name,n", SIZES)
+def test_setting_the_reported_values_changes_nothing(dtype_name, n):
+    from paper_2005_11931_amd import fdw
+
+    dt = fdw.FDW_F64 if dtype_name == "f64" else fdw.FDW_F32
+    case, rec, tg = _problem(n)
+    print("reported values", dtype_name, n, flush=True)
+    s = fdw.solver_for_case(case, dtype=dt)
+    values = [(k, s.config(k)) for k in _keys(fdw)]
+    g0 = s.adjoint(rec, tg, ckpt_every=20).cpu().numpy()
+    s.close()
+    assert np.abs(g0).max() > 0
+    for settings in [[v] for v in values] + [values]:
+        assert np.array_equal(g0, _gradient(case, dt, rec, tg, settings)), settings
+
+
+@pytest.mark.parametrize("dtype_name,n", SIZES)
+def test_tuned_values_set_again_give_the_tuned_sweep(dtype_name, n, tmp_path, monkeypatch):
+    from paper_2005_11931_amd import fdw
+
+    dt = fdw.FDW_F64 if dtype_name == "f64" else fdw.FDW_F32
+    case, rec, tg = _problem(n)
+    monkeypatch.setenv("FDW_AUTOTUNE_CACHE", str(tmp_path / "tune.txt"))
+    print("tuned values", dtype_name, n, flush=True)
+    s = fdw.solver_for_case(case, dtype=dt)
+    s.configure(fdw.FDW_CFG_ADJ_TIME_BLOCK, 3)  # (the tuner takes over from the caller's setting)
+    tuned = s.autotune_adjoint(rec, tg, ckpt_every=20)
+    g = s.adjoint(rec, tg, ckpt_every=20).cpu().numpy()
+    for k, v in zip(_keys(fdw), tuned):
+        s.configure(k, v)
+    assert np.array_equal(g, s.adjoint(rec, tg, ckpt_every=20).cpu().numpy())
+    s.close()
+    assert np.array_equal(g, _gradient(case, dt, rec, tg, list(zip(_keys(fdw), tuned))))
+
+
+@pytest.mark.parametrize("dtype_name", ["f64", "f32"])
+@pytest.mark.parametrize("triple", [(3, 32, 0), (4, 16, 1), (6, 64, 0)])  # block, rows, wide lane layout
+def test_cached_choice_is_the_sweep_that_runs(dtype_name, triple, tmp_path, monkeypatch):
+    """The triple of the tuner's file is applied to the streaming sweep: the gradient has the bits of
+    the same settings made by hand, and agrees with the default's to rounding (FP64: 1e-12 of the
+    largest value, sums of 40 x 4 products over another order; FP32: the same products, each rounded
+    from states that are the same bit for bit: the same bound)."""
+    from paper_2005_11931_amd import fdw
+
+    dt = fdw.FDW_F64 if dtype_name == "f64" else fdw.FDW_F32
+    narrow = 1 if dt == fdw.FDW_F64 else 2
+    K, S, C = triple[0], triple[1], 2 * narrow if triple[2] else narrow
+    case, rec, tg = _problem(384)
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("FDW_AUTOTUNE_CACHE", str(cache))
+    streaming = (fdw.FDW_CFG_SMALL_TILES, 1)
+    print("cached choice", dtype_name, triple, flush=True)
+    s = fdw.solver_for_case(case, dtype=dt)
+    s.autotune_adjoint(rec, tg, ckpt_every=20)
+    s.close()
+    text = cache.read_text()
+    cache.write_text(text[: text.rindex("|") + 1] + f"{K} {S} {C} 0\n")
+    s = fdw.solver_for_case(case, dtype=dt)
+    s.configure(*streaming)
+    assert s.autotune_adjoint(rec, tg, ckpt_every=20) == (K, S, C)
+    assert [s.config(k) for k in _keys(fdw)] == [K, S, C]
+    g = s.adjoint(rec, tg, ckpt_every=20).cpu().numpy()
+    s.close()
+    assert np.array_equal(g, _gradient(case, dt, rec, tg, [streaming, *zip(_keys(fdw), (K, S, C))]))
+    g0 = _gradient(case, dt, rec, tg)
+    assert np.abs(g - g0).max() <= 1e-12 * np.abs(g0).max()
