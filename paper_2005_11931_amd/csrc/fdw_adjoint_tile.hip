@@ -106,15 +106,23 @@ __global__ __launch_bounds__(kWaveSize * (RW == 4 ? kMaxAdjTileWaves : 8)) void 
         }
         FYup = ay * (hr[0] + hr[1]);
     }
-    double g1[RW], g2[RW];  // accumulator rows
+    // Accumulator rows: requested with the states, except eight rows of doubles, which do not fit the 256
+    // registers of two waves per SIMD through the levels (10 registers spilled, 26 with separate gradients;
+    // 400 reverse steps at 700^2: 1.29 -> 1.23 ms, separate gradients 1.51 -> 1.31; 1000^2: 2.28 -> 2.21 and
+    // 2.70 -> 2.40).
+    constexpr bool late_g = sizeof(T) == 8 && RW == 8;
+    double g1[RW], g2[RW];
+    auto load_g = [&](int i) {
+        g1[i] = at_g(rg1, g0 + i);
+        g2[i] = split ? at_g(rg2, g0 + i) : 0.0;
+    };
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
         u[i] = at(ru, g0 + i);
         d[i] = at(rd, g0 + i);
         l[i] = at(rl, g0 + i);
         m[i] = at(rm, g0 + i);
-        g1[i] = at_g(rg1, g0 + i);
-        g2[i] = split ? at_g(rg2, g0 + i) : 0.0;
+        if constexpr (!late_g) load_g(i);
     }
     // adjoint sources: every copy of a receiver node (halo included) takes its source, requested one
     // level ahead; no two receivers share a node here.  Lanes without one load 0 (out of range).
@@ -201,6 +209,10 @@ __global__ __launch_bounds__(kWaveSize * (RW == 4 ? kMaxAdjTileWaves : 8)) void 
         }
     }
 
+    if constexpr (late_g) {
+#pragma unroll
+        for (int i = 0; i < RW; ++i) load_g(i);
+    }
     // y face sums of the row above each wave
     __syncthreads();
     double* const s_y = reinterpret_cast<double*>(smem);  // [NW][64]

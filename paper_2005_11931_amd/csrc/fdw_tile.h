@@ -14,7 +14,7 @@ constexpr int kTileRowsPerWave = 4;
 constexpr int kTileHalo = kMaxTimeBlock;
 constexpr int kTileCols = kWaveSize - 2 * kTileHalo;
 constexpr int kMaxTileWaves = 16;
-constexpr int kMaxAdjTileWaves = 12;  // the reverse tile holds 168 registers per lane
+constexpr int kMaxAdjTileWaves = 12;  // 4-row waves of the reverse tile: 90 to 150 registers per lane, 168 at most
 
 #ifdef __HIPCC__
 // Receiver of every lane in RW rows g0.. of a wave (-1: none): the first of each run of coincident
