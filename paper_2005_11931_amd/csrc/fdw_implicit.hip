@@ -34,9 +34,10 @@
 
 namespace {
 
-// longest line (interior unknowns): 272 / 528 chunks of 16
+// longest line (interior unknowns): in FP64 544 chunks of 8, in FP32 528 chunks of 16 (launch_x)
 template <typename T>
 constexpr int max_line_unknowns() { return sizeof(T) == 8 ? 4352 : 8448; }
+constexpr int kMaxXThreads = 576;  // threads of an x-line workgroup, at most
 constexpr int kStripUnknowns = 1024;            // y lines up to here: one kernel (see launch_y)
 constexpr int kBlockChunk = 8, kBlockChunks = 8;  // beyond: blocks of 8 chunks of 8 rows
 constexpr size_t kAdiAlign = 256;
@@ -235,7 +236,7 @@ int x_line_lds_elems(int P, int threads)
 // and the row's system is solved; one workgroup per row.  Every thread forms the right-hand
 // sides of 16 bytes of consecutive nodes at a time.
 template <typename T, int MT>
-__global__ __launch_bounds__(576) void k_adi_x(LineArgs A)
+__global__ __launch_bounds__(kMaxXThreads) void k_adi_x(LineArgs A)
 {
     extern __shared__ unsigned char smem[];
     constexpr int V = 16 / (int)sizeof(T);
@@ -655,14 +656,15 @@ hipError_t launch_x_mt(const fdw_adi* s, LineArgs A, hipStream_t st)
 // Chunk length of the x lines.  Short chunks give a line more threads, long ones a smaller reduced
 // system: 4 unknowns up to 512 (256^2 FP64: 9.6 us per step against 10.1 with 8), then 8
 // (2048^2 FP64: 79.2 us per step, 81.3 with 4, 77.9 with 16; 4096^2 FP64: 314, 322 with 16); 16 for
-// the FP32 lines that 576 threads of 8 do not cover.
+// the lines that 576 threads of 8 do not cover, which only FP32 has.
 template <typename T>
 hipError_t launch_x(const fdw_adi* s, const LineArgs& A, hipStream_t st)
 {
     const int n = s->nx - 2;
     if (n <= 512) return launch_x_mt<T, 4>(s, A, st);
-    if (n + 1 <= 8 * 576) return launch_x_mt<T, 8>(s, A, st);
-    return launch_x_mt<T, 16>(s, A, st);
+    if constexpr (max_line_unknowns<T>() + 1 > 8 * kMaxXThreads)
+        if (n + 1 > 8 * kMaxXThreads) return launch_x_mt<T, 16>(s, A, st);
+    return launch_x_mt<T, 8>(s, A, st);
 }
 
 template <typename T, bool START>
@@ -701,8 +703,8 @@ hipError_t launch_y_strips(const fdw_adi* s, LineArgs A, hipStream_t st)
     return hipGetLastError();
 }
 
-// Columns of up to 1024 unknowns go through one kernel that holds a strip's whole columns (their
-// strips are 4 to 8 columns wide there, and one launch is shorter than three: 700^2 FP64 19.8 us
+// Columns of up to 1024 unknowns go through one kernel that holds a strip's whole columns (strips of
+// 1 to 8 columns, launch_y_strips, and one launch is shorter than three: 700^2 FP64 19.8 us
 // per step against 24.7 in blocks, 3900 x 1000 FP64 74 against 81); longer ones in blocks of 64
 // rows, with full cache lines (500 x 4000 FP64 48 against 66; 1000 x 1500 FP32 25.1 against 31;
 // 4096^2 FP64 314 against 644).
