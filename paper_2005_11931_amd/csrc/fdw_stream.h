@@ -463,13 +463,15 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
     // a branch in the loop took 16 to 40.  Not in FP32 with faces and energies, where it costs the third
     // wave per SIMD (166 -> 177 registers); with U > K the first block already holds own rows.
     constexpr bool kHead = U <= K && !(sizeof(T) == 4 && FACE && want_energy);
-    if constexpr (kHead) {
+    // Two variants lose a wave per SIMD to the object itself and have the block in the loop (see there)
+    constexpr bool kObject = !(sizeof(T) == 4 && FACE && want_energy && (K == 8 || (C == 4 && K == 6)));
+    if constexpr (kObject) {
         auto rows = [&](auto head_tag, int blk) __attribute__((always_inline)) {
             constexpr bool HEAD = decltype(head_tag)::value;
 #include "fdw_stream_rows.h"
         };
-        rows(BoolTag<true>{}, 0);
-        for (int blk = 1; blk < nblk; ++blk) rows(BoolTag<false>{}, blk);
+        if constexpr (kHead) rows(BoolTag<true>{}, 0);
+        for (int blk = kHead ? 1 : 0; blk < nblk; ++blk) rows(BoolTag<false>{}, blk);
     } else {
         constexpr bool HEAD = false;
         for (int blk = 0; blk < nblk; ++blk) {

@@ -1,10 +1,11 @@
 // fdw_stream_rows.h - one block of U rows of a streaming work item: the body of the row loop of
-// sweep_item (fdw_stream.h), whose names it uses.  It stands in two places there - in a function
-// object for the variants that shorten their first block (HEAD), in the loop itself for the others -
-// and is a file of its own because the two cost different registers: the object takes 173 instead of 166
-// in FP32 with faces and energies, which need 168 for the third wave per SIMD (1531 x 1177, 80 steps:
-// 426 us as an object, 351 in the loop), and 262 instead of 253 in its form with 4 columns per lane
-// (time block 6, 1500^2, 96 steps: 678 and 515 us).
+// sweep_item (fdw_stream.h), whose names it uses.  It stands in two places there and is a file of its own
+// because the two cost different registers.  Most variants have it in a function object, which can
+// shorten the first block (HEAD), and are as fast or faster that way (FP32 time block 7 with energies at
+// 1200^2, 84 steps: 332 us, 370 in the loop).  In FP32 with faces and energies the object takes 173
+// registers instead of 166, beyond the 168 of three waves per SIMD (1531 x 1177, 80 steps: 426 us as an
+// object, 351 in the loop), and 262 instead of 253 with 4 columns per lane at time block 6, beyond the 256
+// of two (1500^2, 96 steps: 678 and 515): these have it in the loop itself.
 {
     T eb[K];
 #pragma unroll
