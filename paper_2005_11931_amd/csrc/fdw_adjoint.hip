@@ -47,6 +47,7 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     constexpr int NB = (sizeof(T) == 8 && C == 1 && K % 3 == 0) ? 3 : 2;
     constexpr int U = (K % 2 == 0) ? K : 2 * K;
     static_assert(U % NB == 0 && U % K == 0 && U % 2 == 0, "row unroll");
+    static_assert(stores_padding(Wv, C), "the last strip stores the padding that is loaded");
     const int lane = threadIdx.x & 63;
     // XCD-contiguous block order, as in the forward kernel: neighbouring strips and segments
     // (which read each other's halo rows and columns) then share an L2
@@ -57,8 +58,8 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void k_adjoint(AdjArgs 
     const int strip = wave % a.strips;
     const int seg = wave / a.strips;
     const int cb = strip * Wv - Hx + lane * C;
-    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
-    // up to three that share a wider lane vector with the last column are written (as 0).
+    // Lanes that start past the grid take 0 whatever the padding holds (checkpoint slots are not cleared);
+    // the up to three columns that share a lane vector with the last one are stored (as 0) and loaded.
     const bool lane_live = (cb >= 0) && (cb < nx);
     const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane * C >= Hx) && (lane * C < Hx + Wv);
     T colm[C];

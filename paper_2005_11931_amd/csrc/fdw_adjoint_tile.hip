@@ -42,8 +42,8 @@ __global__ __launch_bounds__(kWaveSize * (RW == 4 ? kMaxAdjTileWaves : 8)) void 
     const int strip = tile % a.strips;
     const int seg = tile / a.strips;
     const int cb = strip * kTileCols - kTileHalo + lane;
-    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
-    // up to three that share a wider lane vector with the last column are written (as 0).
+    // Lanes that start past the grid take 0 whatever the padding holds (checkpoint slots are not cleared);
+    // the up to three columns that share a lane vector with the last one are stored (as 0) and loaded.
     const bool lane_live = (cb >= 0) && (cb < nx);
     const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane >= kTileHalo) && (lane < kTileHalo + kTileCols);
     const T colm = ((cb >= 1) && (cb <= nx - 2)) ? T(1) : T(0);

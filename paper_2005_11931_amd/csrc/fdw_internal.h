@@ -3,7 +3,11 @@
 // Layout in HBM: every field of a member is a pitched plane [ny][ld] in the storage type
 // (float or double), x fastest, ld = nx rounded up to a multiple of 64 elements so that
 // every row starts on a 256-byte boundary and a wave's C-element lane vectors are aligned.
-// Columns nx..ld-1 and the boundary ring hold 0 at all times.
+// Columns nx..ld-1 and the boundary ring hold 0, except that checkpoint slots (not cleared when a forward
+// run starts to record into them) are undefined from the column on where no lane vector starts inside
+// the grid: nx rounded up to 4 floats or 2 doubles.  So lanes that start past the grid take 0 instead
+// of loading, the vector that straddles nx is loaded, and every kernel that writes a state stores the 0
+// of its columns past nx too, which the widths of the strips cover (stores_padding).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -15,6 +19,10 @@ constexpr int kMaxTimeBlock = 8;      // time steps fused in one streaming launc
 constexpr int kMaxEnergySlots = 64;   // time blocks whose energy partials one finalisation sums
 constexpr int kWaveSize = 64;         // CDNA wavefront
 constexpr int kWavesPerBlock = 4;     // independent streaming waves per workgroup
+
+// Strips of `owned` columns, C per lane (doubles: 1 or 2, floats: 2 or 4), end on a boundary of the widest
+// lane vector of their type, so that the last strip stores the padding that this vector may load.
+constexpr bool stores_padding(int owned, int C) { return owned % (C == 1 ? 2 : 4) == 0; }
 constexpr int kMaxReceivers = 16384;  // per member
 constexpr int kRedBlocks = 1024;      // blocks of the generic two-stage reductions
 // persistent batched launch: at most this many time blocks per launch; its control words are

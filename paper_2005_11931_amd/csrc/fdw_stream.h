@@ -279,14 +279,15 @@ __device__ __forceinline__ void sweep_item(const MemberDev& M, int wave, int par
     constexpr int U = RowUnroll<K>::U;
     constexpr int NB = RowUnroll<K>::NB;
     static_assert(U % NB == 0 && U % K == 0 && U % 2 == 0, "row unroll");
+    static_assert(stores_padding(Wv, C), "the last strip stores the padding that is loaded");
     const int lane = threadIdx.x & 63;
 
     const int nx = M.nx, ny = M.ny, ld = M.ld;
     const int strip = wave % M.strips;
     const int seg = wave / M.strips;
     const int cb = strip * Wv - Hx + lane * C;
-    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
-    // up to three that share a wider lane vector with the last column are written (as 0).
+    // Lanes that start past the grid take 0 whatever the padding holds (checkpoint slots are not cleared);
+    // the up to three columns that share a lane vector with the last one are stored (as 0) and loaded.
     const bool lane_live = (cb >= 0) && (cb < nx);
     const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane * C >= Hx) && (lane * C < Hx + Wv);
     T colm[C];  // 1 on interior columns, 0 on the boundary ring / padding

@@ -13,6 +13,7 @@ namespace fdw {
 constexpr int kTileRowsPerWave = 4;
 constexpr int kTileHalo = kMaxTimeBlock;
 constexpr int kTileCols = kWaveSize - 2 * kTileHalo;
+static_assert(stores_padding(kTileCols, 2), "the last tile stores the padding that is loaded (both types)");
 constexpr int kMaxTileWaves = 16;
 constexpr int kMaxAdjTileWaves = 12;  // 4-row waves of the reverse tile: 90 to 150 registers per lane, 168 at most
 

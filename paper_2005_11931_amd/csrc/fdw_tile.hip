@@ -68,8 +68,8 @@ __device__ __forceinline__ void tile_block(const StepArgs& a, int K)
     const int strip = tile % strips;
     const int seg = tile / strips;
     const int cb = strip * kTileCols - kTileHalo + lane;  // grid column of this lane
-    // Columns past the grid read 0 whatever the padding holds (checkpoint slots are not cleared); the
-    // up to three that share a wider lane vector with the last column are written (as 0).
+    // Lanes that start past the grid take 0 whatever the padding holds (checkpoint slots are not cleared);
+    // the up to three columns that share a lane vector with the last one are stored (as 0) and loaded.
     const bool lane_live = (cb >= 0) && (cb < nx);
     const bool lane_owned = (cb >= 0) && (cb < ((nx + 3) & ~3)) && (lane >= kTileHalo) && (lane < kTileHalo + kTileCols);
     const T colm = ((cb >= 1) && (cb <= nx - 2)) ? T(1) : T(0);

@@ -71,6 +71,28 @@ def test_tuned_values_set_again_give_the_tuned_sweep(dtype_name, n, tmp_path, mo
 
 
 @pytest.mark.parametrize("dtype_name", ["f64", "f32"])
+def test_reverse_blocks_of_every_length(dtype_name):
+    """The streaming sweep between checkpoints ck steps apart runs blocks of 8 (FP64) or 6 (FP32) and a
+    remainder of every length (7 as 4 + 3), whose first block of rows is shortened where its length is
+    even: gradients agree to the rounding of their sums (33 x 4 products, 1e-12 of the largest value)."""
+    from paper_2005_11931_amd import fdw
+
+    dt = fdw.FDW_F64 if dtype_name == "f64" else fdw.FDW_F32
+    case, rec, tg = _problem(211, nsteps=33)
+    print("reverse blocks", dtype_name, flush=True)
+    got = []
+    for ck in (1, *range(9, 17)):
+        s = fdw.solver_for_case(case, dtype=dt)
+        s.configure(fdw.FDW_CFG_SMALL_TILES, 1)
+        got.append(s.adjoint(rec, tg, ckpt_every=ck).cpu().numpy())
+        s.close()
+    assert np.abs(got[0]).max() > 0
+    tol = 1e-12 if dt == fdw.FDW_F64 else 1e-4  # FP32: the states are rebuilt from other checkpoints
+    for g in got[1:]:
+        assert np.abs(g - got[0]).max() <= tol * np.abs(got[0]).max()
+
+
+@pytest.mark.parametrize("dtype_name", ["f64", "f32"])
 @pytest.mark.parametrize("triple", [(3, 32, 0), (4, 16, 1), (6, 64, 0)])  # block, rows, wide lane layout
 def test_cached_choice_is_the_sweep_that_runs(dtype_name, triple, tmp_path, monkeypatch):
     """The triple of the tuner's file is applied to the streaming sweep: the gradient has the bits of
