@@ -310,8 +310,8 @@ bool stream_nt(const fdw_ctx* c);
 // n = ceil(workgroups / CUs) of the items (one wave of each workgroup): (S + 2K) n f(n), f the cost of the
 // dependent chains that too few waves cannot overlap (n = 1: 1.7, n = 2: 1.1).  The S of least cost
 // from 8 to 16 K, over all members of a launch, summed over the launches; measured within 4% of the
-// best S at every size tried (1300^2 FP64 with energies 4.09 us per step against 5.42 before, 2048^2 FP64 5.01 / 5.47, with
-// energies 5.78 / 7.30, 2900^2 FP32 with energies 5.35 / 7.12, 700 x 4000 FP32 2.77 / 3.68).
+// best S at every size tried (1300^2 FP64 with energies 4.09 us per step against 5.42 before, 2048^2
+// FP64 5.01 / 5.47, with energies 5.78 / 7.30, 700 x 4000 FP32 2.77 / 3.68).
 // Other launches keep the earlier rule (plain_S): 16 K rows, fewer where that leaves less than about
 // 4600 waves for the largest member: planes streamed from memory (stream_nt; 8192^2 FP32: 0.275 ms per
 // launch at 128 rows, 0.292 to 0.297 at 100 to 208), the persistent launch (whose waves take items
